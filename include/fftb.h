@@ -100,7 +100,9 @@ typedef struct {
   int32_t nbands;      /* >= 1 bands sharing this map */
 } fftb_sphere;
 
-/* Tiling of one direction. A zero field means "library default". */
+/* Tiling of one direction. A zero field means "library default". With every
+ * field zero the library may also choose axis passes (one kernel per axis, no
+ * class split); such a direction reports all fields zero in fftb_plan_info. */
 typedef struct {
   int32_t band_chunk;   /* bands per workgroup tile, power of two, 1..64; path 3 takes one
                            128-byte piece (16 complex64 / 8 complex128 bands), and for the
@@ -247,7 +249,9 @@ fftb_status fftb_plan_sphere_columns(fftb_plan plan, int32_t sphere, int32_t* co
  * the execute stream around each kernel launch (not available for graph
  * replays). Index 0: column kernel, inverse; 1: plane kernel, inverse;
  * 2: plane kernel, forward; 3: column kernel, forward; 4: class combine,
- * forward (plans whose forward plane kernel writes class partials). */
+ * forward (plans whose forward plane kernel writes class partials). A direction
+ * that runs as axis passes counts its z pass as the column kernel and its y and
+ * x passes together as one launch of the plane kernel. */
 typedef struct {
   int64_t launches[5];
   double total_ms[5];

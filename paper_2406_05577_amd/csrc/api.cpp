@@ -20,6 +20,7 @@
 
 #include "../../include/fftb.h"
 #include "kargs.hpp"
+#include "pass.hpp"
 #include "plan.hpp"
 
 namespace fftb {
@@ -41,6 +42,9 @@ hipError_t launch_bil(int which, const KArgs& a, bool inverse, bool fp64, int E,
                       int threads, size_t lds, hipStream_t st, int fold_m);
 hipError_t prepare_bil(bool fp64, int E, int H, size_t lds, bool narrow);
 hipError_t launch_zero_scratch(void* p, size_t bytes, hipStream_t st);
+hipError_t launch_pass(bool inverse, bool fp64, int n, const PassArgs& a, int threads, size_t lds,
+                       hipStream_t st);
+hipError_t prepare_pass(bool inverse, bool fp64, int n, size_t lds);
 }  // namespace fftb
 
 using namespace fftb;
@@ -107,7 +111,8 @@ struct DirCfg {
   AxisPlan ay;                      // y plan of length m
   std::vector<SphereDesc> desc;
   int k1_tasks = 0, k2_tasks = 0, k3_tasks = 0;
-  int64_t col_elems = 0;
+  int64_t col_elems = 0;            // scratch of the class-split kernels
+  bool pass = false;                // runs as axis passes instead
   SphereDesc* d_desc = nullptr;
   int32_t* d_splits = nullptr;
   void* d_twy = nullptr;
@@ -140,6 +145,11 @@ struct fftb_plan_s {
   int pad_m = 0;
   std::vector<int32_t> col_slot, slab_blk, slab_nblk, colidx_slot;  // concatenated over spheres
   std::vector<int32_t> npcol;                            // per sphere
+  // axis passes (directions with DirCfg::pass)
+  PassPlan pp;
+  int64_t pass_at = 0;  // their column scratch within d_col (elements), the slab scratch after it
+  PassSph* d_psph = nullptr;
+  int32_t *d_pgidx = nullptr, *d_pcolidx = nullptr, *d_pxinv = nullptr;
   void *d_twx = nullptr, *d_twz = nullptr, *d_twf = nullptr;
   void *d_twx_lo = nullptr, *d_twz_lo = nullptr, *d_twf_lo = nullptr;
   void *d_rootx = nullptr, *d_rootx_lo = nullptr, *d_rootz = nullptr, *d_rootz_lo = nullptr;
@@ -155,6 +165,14 @@ struct fftb_plan_s {
     const void* pot = nullptr;
   } gc[2];
   hipStream_t cap_stream = nullptr;
+  bool uses_pass() const { return dir[0].pass || dir[1].pass; }
+  bool uses_classes() const { return !dir[0].pass || !dir[1].pass; }
+  // elements of the scratch d_col: the class-split regions of the directions
+  // that use them, then the passes' columns and slab planes
+  int64_t class_elems(int d) const { return dir[d].pass ? 0 : dir[d].col_elems; }
+  int64_t scratch_elems() const {
+    return class_elems(0) + class_elems(1) + (uses_pass() ? pp.col_elems + pp.s_elems() : 0);
+  }
   // per-kernel timing
   bool profiling = false;
   struct ProfRec {
@@ -371,7 +389,7 @@ int default_bc(const fftb_plan_s& P, int want) {
   return std::min(want, cap);
 }
 
-fftb_status choose_dir(fftb_plan_s& P, int d, const fftb_dir_tuning& t) {
+fftb_status choose_tiling(fftb_plan_s& P, int d, const fftb_dir_tuning& t) {
   DirCfg& D = P.dir[d];
   const bool fp64 = P.dtype == FFTB_C128;
   const bool inverse = d == 0;
@@ -735,6 +753,50 @@ fftb_status choose_dir(fftb_plan_s& P, int d, const fftb_dir_tuning& t) {
   return FFTB_OK;
 }
 
+// Tiling of one direction: the class-split kernels' (which also decides what is
+// refused), and whether the direction runs as axis passes instead. Those take
+// every plan that asks for no tiling, has lines of at most 512 points and has no
+// band-inner x shape: its class-split kernels would be the LDS-stage or the
+// register ones, which re-read or re-transform per y class (round trips, class
+// split -> passes: 108x100x120, 50 complex64 bands, 7.50 -> 0.68 ms;
+// 200x192x216, 20 complex128 bands, 87.4 -> 2.69 ms; 256^3, 24 complex128 bands
+// on register lines, 10.8 -> 6.69 ms).
+fftb_status choose_dir(fftb_plan_s& P, int d, const fftb_dir_tuning& t) {
+  DirCfg& D = P.dir[d];
+  D.pass = false;
+  const fftb_status st = choose_tiling(P, d, t);
+  if (st != FFTB_OK) return st;
+  const fftb_dir_tuning none = {};
+  D.pass = std::memcmp(&t, &none, sizeof t) == 0 && !D.bil2 && !(P.flags & FFTB_PLAN_MFMA) &&
+           P.nx <= kPassMaxN && P.ny <= kPassMaxN && P.nz <= kPassMaxN;
+  return FFTB_OK;
+}
+
+// Slab scratch of one y/x group: what stays in the 256 MB last-level cache
+// between the two passes beside the grid's stream (streamed past it).
+constexpr int64_t kSlabBudget = int64_t{128} << 20;
+
+// Build the pass plan of the directions that chose passes; they fall back to
+// the class-split kernels where it does not fit.
+void setup_passes(fftb_plan_s& P) {
+  if (!P.uses_pass()) return;
+  const int64_t es = es_of(P.dtype);
+  const size_t cap = device_byte_cap();
+  // a z plane of columns takes no more than in the class-split layouts
+  std::vector<int64_t> row_max(P.sph.size(), INT64_MAX);
+  for (const DirCfg& D : P.dir)
+    for (size_t i = 0; i < P.sph.size(); ++i)
+      row_max[i] = std::min(row_max[i], static_cast<int64_t>(D.desc[i].nbp) * D.desc[i].npcol);
+  bool ok = build_pass_plan(P.nx, P.ny, P.nz, P.dtype == FFTB_C128, P.sph, row_max, kSlabBudget, P.pp);
+  if (ok && cap) {
+    // under a device memory bound: no more scratch than the class-split kernels
+    const int64_t room = P.dir[0].col_elems + P.dir[1].col_elems - P.pp.col_elems;
+    ok = !P.uses_classes() && room >= P.pp.splane;
+    if (ok) P.pp.group = static_cast<int>(std::min<int64_t>(P.pp.group, room / P.pp.splane));
+  }
+  if (!ok) P.dir[0].pass = P.dir[1].pass = false;
+}
+
 void fill_axis(const AxisPlan& a, AxisDev& d) {
   std::memset(&d, 0, sizeof d);
   d.n = a.n;
@@ -921,7 +983,20 @@ fftb_status device_setup(fftb_plan_s& P, hipStream_t st) {
     return fail(FFTB_ERR_HIP, std::string("hipGetDeviceProperties: ") + hipGetErrorString(e));
   P.num_cus = prop.multiProcessorCount;
   std::vector<int32_t> gidx, colxi, coly, xinv, slabstart, slaborder;
+  fftb_status s;
+  void* p;
+  if (P.uses_pass()) {
+    if ((s = upload(P, P.pp.sph, &p, st)) != FFTB_OK) return s;
+    P.d_psph = static_cast<PassSph*>(p);
+    if ((s = upload(P, P.pp.gidx, &p, st)) != FFTB_OK) return s;
+    P.d_pgidx = static_cast<int32_t*>(p);
+    if ((s = upload(P, P.pp.colidx, &p, st)) != FFTB_OK) return s;
+    P.d_pcolidx = static_cast<int32_t*>(p);
+    if ((s = upload(P, P.pp.xinv, &p, st)) != FFTB_OK) return s;
+    P.d_pxinv = static_cast<int32_t*>(p);
+  }
   for (auto& s : P.sph) {
+    if (!P.uses_classes()) break;
     slaborder.insert(slaborder.end(), s.slab_order.begin(), s.slab_order.end());
     gidx.insert(gidx.end(), s.gidx.begin(), s.gidx.end());
     colxi.insert(colxi.end(), s.col_xi.begin(), s.col_xi.end());
@@ -929,42 +1004,42 @@ fftb_status device_setup(fftb_plan_s& P, hipStream_t st) {
     xinv.insert(xinv.end(), s.xinv.begin(), s.xinv.end());
     slabstart.insert(slabstart.end(), s.slabstart.begin(), s.slabstart.end());
   }
-  fftb_status s;
-  void* p;
   for (auto& D : P.dir) {
+    if (D.pass) continue;
     if ((s = upload(P, D.desc, &p, st)) != FFTB_OK) return s;
     D.d_desc = static_cast<SphereDesc*>(p);
     if ((s = upload(P, D.splits, &p, st)) != FFTB_OK) return s;
     D.d_splits = static_cast<int32_t*>(p);
     if ((s = upload_tw(P, axis_twiddles(D.ay), &D.d_twy, &D.d_twy_lo, st)) != FFTB_OK) return s;
   }
-  if ((s = upload(P, gidx, &p, st)) != FFTB_OK) return s;
-  P.d_gidx = static_cast<int32_t*>(p);
-  if ((s = upload(P, P.colidx_slot, &p, st)) != FFTB_OK) return s;
-  P.d_colidx = static_cast<int32_t*>(p);
-  if ((s = upload(P, colxi, &p, st)) != FFTB_OK) return s;
-  P.d_colxi = static_cast<int32_t*>(p);
-  if ((s = upload(P, coly, &p, st)) != FFTB_OK) return s;
-  P.d_coly = static_cast<int32_t*>(p);
-  if ((s = upload(P, xinv, &p, st)) != FFTB_OK) return s;
-  P.d_xinv = static_cast<int32_t*>(p);
-  if ((s = upload(P, slabstart, &p, st)) != FFTB_OK) return s;
-  P.d_slabstart = static_cast<int32_t*>(p);
-  if ((s = upload(P, P.col_slot, &p, st)) != FFTB_OK) return s;
-  P.d_colslot = static_cast<int32_t*>(p);
-  if ((s = upload(P, P.slab_blk, &p, st)) != FFTB_OK) return s;
-  P.d_slabblk = static_cast<int32_t*>(p);
-  if ((s = upload(P, P.slab_nblk, &p, st)) != FFTB_OK) return s;
-  P.d_slabnblk = static_cast<int32_t*>(p);
-  if ((s = upload(P, slaborder, &p, st)) != FFTB_OK) return s;
-  P.d_slaborder = static_cast<int32_t*>(p);
-  if ((s = upload_tw(P, axis_twiddles(P.ax), &P.d_twx, &P.d_twx_lo, st)) != FFTB_OK) return s;
-  if ((s = upload_tw(P, axis_twiddles(P.az), &P.d_twz, &P.d_twz_lo, st)) != FFTB_OK) return s;
+  if (P.uses_classes()) {
+    if ((s = upload(P, gidx, &p, st)) != FFTB_OK) return s;
+    P.d_gidx = static_cast<int32_t*>(p);
+    if ((s = upload(P, P.colidx_slot, &p, st)) != FFTB_OK) return s;
+    P.d_colidx = static_cast<int32_t*>(p);
+    if ((s = upload(P, colxi, &p, st)) != FFTB_OK) return s;
+    P.d_colxi = static_cast<int32_t*>(p);
+    if ((s = upload(P, coly, &p, st)) != FFTB_OK) return s;
+    P.d_coly = static_cast<int32_t*>(p);
+    if ((s = upload(P, xinv, &p, st)) != FFTB_OK) return s;
+    P.d_xinv = static_cast<int32_t*>(p);
+    if ((s = upload(P, slabstart, &p, st)) != FFTB_OK) return s;
+    P.d_slabstart = static_cast<int32_t*>(p);
+    if ((s = upload(P, P.col_slot, &p, st)) != FFTB_OK) return s;
+    P.d_colslot = static_cast<int32_t*>(p);
+    if ((s = upload(P, P.slab_blk, &p, st)) != FFTB_OK) return s;
+    P.d_slabblk = static_cast<int32_t*>(p);
+    if ((s = upload(P, P.slab_nblk, &p, st)) != FFTB_OK) return s;
+    P.d_slabnblk = static_cast<int32_t*>(p);
+    if ((s = upload(P, slaborder, &p, st)) != FFTB_OK) return s;
+    P.d_slaborder = static_cast<int32_t*>(p);
+    if ((s = upload_tw(P, axis_twiddles(P.ax), &P.d_twx, &P.d_twx_lo, st)) != FFTB_OK) return s;
+    if ((s = upload_tw(P, axis_twiddles(P.az), &P.d_twz, &P.d_twz_lo, st)) != FFTB_OK) return s;
+  }
   if ((s = upload_tw(P, root_table(P.ny), &P.d_twf, &P.d_twf_lo, st)) != FFTB_OK) return s;
   if ((s = upload_tw(P, root_table(P.nx), &P.d_rootx, &P.d_rootx_lo, st)) != FFTB_OK) return s;
   if ((s = upload_tw(P, root_table(P.nz), &P.d_rootz, &P.d_rootz_lo, st)) != FFTB_OK) return s;
-  const int64_t col_elems = P.dir[0].col_elems + P.dir[1].col_elems;
-  const size_t col_bytes = static_cast<size_t>(col_elems) * es_of(P.dtype);
+  const size_t col_bytes = static_cast<size_t>(P.scratch_elems()) * es_of(P.dtype);
   if (g_tune_scratch) {
     // an autotuning trial: borrow the tuner's scratch (the previous trial has
     // completed; the tuner synchronises after every trial)
@@ -986,7 +1061,8 @@ fftb_status device_setup(fftb_plan_s& P, hipStream_t st) {
   }
   // the padding slots of the inverse's column region must read as zero (no
   // kernel writes them); every other scratch value is written before it is read
-  e = hipMemsetAsync(P.d_col, 0, static_cast<size_t>(P.dir[0].col_elems) * es_of(P.dtype), st);
+  if (P.class_elems(0) > 0)
+    e = hipMemsetAsync(P.d_col, 0, static_cast<size_t>(P.class_elems(0)) * es_of(P.dtype), st);
   if (e != hipSuccess) return fail(FFTB_ERR_HIP, std::string("hipMemsetAsync: ") + hipGetErrorString(e));
   if ((s = dev_alloc(P, 24 * sizeof(unsigned int), &p)) != FFTB_OK) return s;
   P.d_counters = static_cast<unsigned int*>(p);
@@ -994,7 +1070,22 @@ fftb_status device_setup(fftb_plan_s& P, hipStream_t st) {
   if (e != hipSuccess) return fail(FFTB_ERR_HIP, std::string("hipMemsetAsync: ") + hipGetErrorString(e));
   const bool fp64 = P.dtype == FFTB_C128;
   size_t g1 = 4, g2 = 4, r2 = 4;
+  for (int d = 0; d < 2; ++d) {
+    const DirCfg& D = P.dir[d];
+    if (!D.pass) continue;
+    const int n[3] = {P.nx, P.ny, P.nz};
+    const PassTile* tl[3] = {&P.pp.tx, &P.pp.ty, &P.pp.tz};
+    for (int i = 0; i < 3; ++i) {
+      size_t lds = tl[i]->lds;  // axes of one length share the kernel
+      for (int j = 0; j < 3; ++j)
+        if (n[j] == n[i]) lds = std::max(lds, tl[j]->lds);
+      e = prepare_pass(d == 0, fp64, n[i], lds);
+      if (e != hipSuccess)
+        return fail(FFTB_ERR_HIP, std::string("hipFuncSetAttribute: ") + hipGetErrorString(e));
+    }
+  }
   for (auto& D : P.dir) {
+    if (D.pass) continue;
     if (!D.reg1) g1 = std::max(g1, D.lds1);
     if (!D.reg2) g2 = std::max(g2, D.lds2);
     else r2 = std::max(r2, D.lds2);
@@ -1003,7 +1094,7 @@ fftb_status device_setup(fftb_plan_s& P, hipStream_t st) {
   if (e != hipSuccess)
     return fail(FFTB_ERR_HIP, std::string("hipFuncSetAttribute: ") + hipGetErrorString(e));
   for (auto& D : P.dir) {
-    if (!D.reg2) continue;
+    if (D.pass || !D.reg2) continue;
     e = D.bil2 ? prepare_bil(fp64, D.e2, D.h2, r2, D.narrow)
                : prepare_reg(fp64, D.e2, D.h2, r2, D.mf2);
     if (e != hipSuccess)
@@ -1188,19 +1279,131 @@ hipError_t enqueue(fftb_plan_s* P, const KArgs& a, const DirCfg& D, bool inverse
   return hipSuccess;
 }
 
+// Enqueue one direction as axis passes: the z pass over all columns, and the y
+// and x passes over groups of planes whose slab scratch stays in the last-level
+// cache between them. The two together take the profile slot of the plane kernel.
+hipError_t enqueue_pass(fftb_plan_s* P, const void* in, void* out, bool inverse, const void* pot,
+                        void* col, hipStream_t st, bool profile) {
+  const bool fp64 = P->dtype == FFTB_C128;
+  const PassPlan& pp = P->pp;
+  const size_t es = static_cast<size_t>(es_of(P->dtype));
+  void* slab = static_cast<char*>(P->d_col) + static_cast<size_t>(P->pass_at + pp.col_elems) * es;
+  PassArgs base = {};
+  base.nx = P->nx;
+  base.ny = P->ny;
+  base.nz = P->nz;
+  base.nsph = static_cast<int>(pp.sph.size());
+  base.splane = pp.splane;
+  base.sph = P->d_psph;
+  base.scale = 1.0;
+  auto launch = [&](int kind, int p0, int np) {
+    PassArgs a = base;
+    const PassTile& t = kind == kPassZ ? pp.tz : kind == kPassY ? pp.ty : pp.tx;
+    a.kind = kind;
+    a.p0 = p0;
+    a.tiles = t.tiles;
+    a.rtiles = t.rtiles;
+    a.fc = t.fc;
+    a.lines = t.lines;
+    a.lds_tw = t.lds_tw;
+    const void* gat;  // the side reached through the table, and the dense side
+    const void* den;
+    int n;
+    if (kind == kPassZ) {
+      n = P->nz;
+      a.total = pp.ztotal;
+      a.tab = P->d_pgidx;
+      a.root = P->d_rootz;
+      a.root_lo = P->d_rootz_lo;
+      gat = inverse ? in : out;
+      den = col;
+      if (!inverse) a.scale = 1.0 / (static_cast<double>(P->nx) * P->ny * P->nz);
+    } else if (kind == kPassY) {
+      n = P->ny;
+      a.total = np * t.tiles;
+      a.tab = P->d_pcolidx;
+      a.root = P->d_twf;
+      a.root_lo = P->d_twf_lo;
+      gat = col;
+      den = slab;
+      a.nt_gather = 1;
+    } else {
+      n = P->nx;
+      a.total = np * t.tiles * t.rtiles;
+      a.tab = P->d_pxinv;
+      a.root = P->d_rootx;
+      a.root_lo = P->d_rootx_lo;
+      gat = slab;
+      den = inverse ? out : in;
+      a.pot = inverse ? pot : nullptr;
+      a.nt_dense = 1;
+    }
+    a.src = inverse ? gat : den;
+    a.dst = const_cast<void*>(inverse ? den : gat);
+    return launch_pass(inverse, fp64, n, a, t.threads, t.lds, st);
+  };
+  auto timed = [&](int kid, auto&& body) {
+    hipEvent_t ea = nullptr, eb = nullptr;
+    hipError_t e = hipSuccess;
+    if (profile) {
+      if ((e = get_event(P, &ea)) != hipSuccess) return e;
+      if ((e = get_event(P, &eb)) != hipSuccess) return e;
+      if ((e = hipEventRecord(ea, st)) != hipSuccess) return e;
+    }
+    if ((e = body()) != hipSuccess) return e;
+    if (profile) {
+      if ((e = hipEventRecord(eb, st)) != hipSuccess) return e;
+      P->prof_pending.push_back({kid, ea, eb});
+    }
+    return e;
+  };
+  auto planes = [&] {
+    for (int p0 = 0; p0 < pp.nplanes; p0 += pp.group) {
+      const int np = std::min(pp.group, pp.nplanes - p0);
+      hipError_t e = launch(inverse ? kPassY : kPassX, p0, np);
+      if (e == hipSuccess) e = launch(inverse ? kPassX : kPassY, p0, np);
+      if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
+  };
+  if (inverse) {
+    const hipError_t e = timed(0, [&] { return launch(kPassZ, 0, 0); });
+    return e != hipSuccess ? e : timed(1, planes);
+  }
+  const hipError_t e = timed(2, planes);
+  return e != hipSuccess ? e : timed(3, [&] { return launch(kPassZ, 0, 0); });
+}
+
+// Enqueue one direction of a plan with `col` as its column scratch.
+hipError_t enqueue_dir(fftb_plan_s* P, const void* in, void* out, bool inverse, const void* pot,
+                       void* col, hipStream_t st, bool profile) {
+  const DirCfg& D = P->dir[inverse ? 0 : 1];
+  if (D.pass) return enqueue_pass(P, in, out, inverse, pot, col, st, profile);
+  int g1, g2, g3;
+  grids(*P, D, g1, g2, g3);
+  KArgs a = make_args(*P, D, in, out, inverse, pot);
+  a.col = col;
+  return enqueue(P, a, D, inverse, g1, g2, g3, st, profile);
+}
+
+// The plan's own column scratch of one direction (the class-split kernels take
+// the base: their descriptors hold the offsets).
+void* plan_col(fftb_plan_s* P, bool inverse) {
+  if (!P->dir[inverse ? 0 : 1].pass) return P->d_col;
+  return static_cast<char*>(P->d_col) + static_cast<size_t>(P->pass_at) * es_of(P->dtype);
+}
+
 fftb_status run(fftb_plan_s* P, const void* in, void* out, void* stream, bool inverse,
                 const void* pot = nullptr) {
   if (!P) return fail(FFTB_ERR_INVALID, "null plan");
   if (!P->device) return fail(FFTB_ERR_INVALID, "plan was created host-only");
   if (!in || !out) return fail(FFTB_ERR_INVALID, "null data pointer");
   hipStream_t st = static_cast<hipStream_t>(stream);
-  const DirCfg& D = P->dir[inverse ? 0 : 1];
-  int g1, g2, g3;
-  grids(*P, D, g1, g2, g3);
-  KArgs a = make_args(*P, D, in, out, inverse, pot);
+  if (!inverse) pot = nullptr;
+  void* col = plan_col(P, inverse);
   if (P->flags & FFTB_PLAN_GRAPH) {
     auto& gc = P->gc[inverse ? 0 : 1];
-    if (!gc.exec || gc.in != in || gc.out != out || gc.pot != a.pot) {
+    if (!gc.exec || gc.in != in || gc.out != out || gc.pot != pot) {
       if (gc.exec) { (void)hipGraphExecDestroy(gc.exec); gc.exec = nullptr; }
       if (gc.graph) { (void)hipGraphDestroy(gc.graph); gc.graph = nullptr; }
       if (!P->cap_stream) {
@@ -1209,7 +1412,7 @@ fftb_status run(fftb_plan_s* P, const void* in, void* out, void* stream, bool in
       }
       hipError_t e = hipStreamBeginCapture(P->cap_stream, hipStreamCaptureModeThreadLocal);
       if (e != hipSuccess) return fail(FFTB_ERR_HIP, std::string("hipStreamBeginCapture: ") + hipGetErrorString(e));
-      hipError_t el = enqueue(P, a, D, inverse, g1, g2, g3, P->cap_stream, false);
+      hipError_t el = enqueue_dir(P, in, out, inverse, pot, col, P->cap_stream, false);
       e = hipStreamEndCapture(P->cap_stream, &gc.graph);
       if (el != hipSuccess) return fail(FFTB_ERR_HIP, std::string("launch during capture: ") + hipGetErrorString(el));
       if (e != hipSuccess) return fail(FFTB_ERR_HIP, std::string("hipStreamEndCapture: ") + hipGetErrorString(e));
@@ -1217,13 +1420,13 @@ fftb_status run(fftb_plan_s* P, const void* in, void* out, void* stream, bool in
       if (e != hipSuccess) return fail(FFTB_ERR_HIP, std::string("hipGraphInstantiate: ") + hipGetErrorString(e));
       gc.in = in;
       gc.out = out;
-      gc.pot = a.pot;
+      gc.pot = pot;
     }
     hipError_t e = hipGraphLaunch(gc.exec, st);
     if (e != hipSuccess) return fail(FFTB_ERR_HIP, std::string("hipGraphLaunch: ") + hipGetErrorString(e));
     return FFTB_OK;
   }
-  hipError_t e = enqueue(P, a, D, inverse, g1, g2, g3, st, P->profiling);
+  hipError_t e = enqueue_dir(P, in, out, inverse, pot, col, st, P->profiling);
   if (e != hipSuccess) return fail(FFTB_ERR_HIP, std::string("kernel launch: ") + hipGetErrorString(e));
   return FFTB_OK;
 }
@@ -1246,9 +1449,21 @@ void log_plan(const fftb_plan_s& P) {
                static_cast<long long>(P.total_columns), P.dtype == FFTB_C128 ? "complex128" : "complex64",
                P.flags, P.autotuned == 1 ? "autotuned" : P.autotuned == 2 ? "tuning from cache" : "default tiling",
                P.dev_bytes / 1e9,
-               static_cast<double>(P.dir[0].col_elems + P.dir[1].col_elems) * es_of(P.dtype) / 1e9);
+               static_cast<double>(P.scratch_elems()) * es_of(P.dtype) / 1e9);
   for (int d = 0; d < 2; ++d) {
     const DirCfg& D = P.dir[d];
+    if (D.pass) {
+      std::fprintf(stderr, "  %s: axis passes, %d groups of %d planes", d == 0 ? "inverse" : "forward",
+                   (P.pp.nplanes + P.pp.group - 1) / P.pp.group, P.pp.group);
+      const char* name[3] = {"z", "y", "x"};
+      const PassTile* tl[3] = {&P.pp.tz, &P.pp.ty, &P.pp.tx};
+      const int n[3] = {P.nz, P.ny, P.nx};
+      for (int i = 0; i < 3; ++i)
+        std::fprintf(stderr, ", %s %dx%d tile %d elements x %d rows, %d threads, LDS %zu B", name[i],
+                     pass_r1(n[i]), n[i] / pass_r1(n[i]), tl[i]->fc, tl[i]->lines, tl[i]->threads, tl[i]->lds);
+      std::fprintf(stderr, "\n");
+      continue;
+    }
     std::fprintf(stderr,
                  "  %s: band chunk %d, %d y classes of %d, %d threads, column kernel %s (%dx%d, %d "
                  "columns/task, %d tasks), plane kernel %s (%dx%d, LDS %zu B, %d tasks)%s%s, "
@@ -1346,14 +1561,15 @@ void cache_store(uint64_t key, const fftb_tuning& t) {
 // Effective tiling of one direction as choose_dir resolves it (the fields
 // that tell two candidates apart).
 struct DirKey {
-  int v[9];
+  int v[10];
   bool operator==(const DirKey& o) const { return std::memcmp(v, o.v, sizeof v) == 0; }
 };
 DirKey dir_key(const DirCfg& D, bool inverse) {
   DirKey k = {{D.narrow ? D.bc2 : D.bc, D.n1, D.threads,
                (D.reg1 ? 1 : 0) | (D.reg2 ? 2 : 0) | (D.bil1 ? 4 : 0) | (D.bil2 ? 8 : 0),
                D.reg2 ? D.h2 : D.lx,
-               D.lc, inverse ? D.qc : (D.fwd_cls ? 3 : D.acc_lds ? 1 : 2), D.nsplit, D.h1}};
+               D.lc, inverse ? D.qc : (D.fwd_cls ? 3 : D.acc_lds ? 1 : 2), D.nsplit, D.h1,
+               D.pass ? 1 : 0}};
   return k;
 }
 
@@ -1613,13 +1829,16 @@ fftb_status fftb_plan_create(fftb_plan* out, const int32_t dims[3], const fftb_s
     // the scratch holds the inverse's columns first, then the forward's columns
     // and class partials: the inverse fold relies on its zero padding slots,
     // which a forward with another band stride would otherwise overwrite
+    setup_passes(*P);
     for (auto& dd : P->dir[1].desc) {
-      dd.col_off += P->dir[0].col_elems;
-      dd.zp_off += P->dir[0].col_elems;
+      dd.col_off += P->class_elems(0);
+      dd.zp_off += P->class_elems(0);
     }
+    P->pass_at = P->class_elems(0) + P->class_elems(1);
     for (int d = 0; d < 2; ++d) {
       const DirCfg& D = P->dir[d];
       fftb_dir_tuning& o = d == 0 ? P->tun.inv : P->tun.fwd;
+      if (D.pass) continue;  // no class-split tiling in use: all zero
       o.band_chunk = D.narrow ? D.bc2 : D.bc;
       o.y_classes = D.n1;
       o.x_rows = D.lx;
@@ -1633,8 +1852,7 @@ fftb_status fftb_plan_create(fftb_plan* out, const int32_t dims[3], const fftb_s
     }
     if (!(flags & FFTB_PLAN_HOST_ONLY)) {
       const size_t cap = device_byte_cap();
-      const size_t scratch = static_cast<size_t>(P->dir[0].col_elems + P->dir[1].col_elems) *
-                             es_of(dtype);
+      const size_t scratch = static_cast<size_t>(P->scratch_elems()) * es_of(dtype);
       if (cap && !g_tune_scratch && scratch > cap)
         return fail(FFTB_ERR_NOMEM, "plan scratch of " + std::to_string(scratch) +
                                         " bytes exceeds FFTB_MAX_DEVICE_BYTES");
@@ -1686,14 +1904,12 @@ fftb_status fftb_sphere_to_grid_static(fftb_plan P, const void* sphere_in, void*
       return fail(FFTB_ERR_HIP, std::string("hipGetSymbolAddress: ") + hipGetErrorString(e));
     hipStream_t st = static_cast<hipStream_t>(stream);
     // the padding slots the inverse fold reads must be zero; the array keeps
-    // the previous call's contents (col_elems * value size is a multiple of 16)
-    e = launch_zero_scratch(scr, (need + 15) & ~size_t{15}, st);
+    // the previous call's contents (col_elems * value size is a multiple of
+    // 16). The axis passes read what they wrote, and no more of it than the
+    // class-split columns would take.
+    if (!D.pass) e = launch_zero_scratch(scr, (need + 15) & ~size_t{15}, st);
     if (e != hipSuccess) return fail(FFTB_ERR_HIP, std::string("kernel launch: ") + hipGetErrorString(e));
-    int g1, g2, g3;
-    grids(*P, D, g1, g2, g3);
-    KArgs a = make_args(*P, D, sphere_in, grid_out, true, nullptr);
-    a.col = scr;
-    e = enqueue(P, a, D, true, g1, g2, g3, st, false);
+    e = enqueue_dir(P, sphere_in, grid_out, true, nullptr, scr, st, false);
     if (e != hipSuccess) return fail(FFTB_ERR_HIP, std::string("kernel launch: ") + hipGetErrorString(e));
     return FFTB_OK;
   } catch (...) {

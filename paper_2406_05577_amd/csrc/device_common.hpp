@@ -367,6 +367,10 @@ __device__ __forceinline__ void dft(cpx<T>* v) {
     dft_pfa<4, 5, S>(v);
   } else if constexpr (R == 24) {
     dft_pfa<8, 3, S>(v);
+  } else if constexpr (R == 25) {
+    dft_ab<5, 5, S>(v);
+  } else if constexpr (R == 27) {
+    dft_ab<9, 3, S>(v);
   } else if constexpr (R == 32) {
     dft_ab<8, 4, S>(v);
   } else if constexpr (R == 36) {

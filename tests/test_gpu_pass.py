@@ -1,0 +1,89 @@
+"""GPU parity of the axis passes: the lengths where their two stages can go
+wrong (single stage, the smallest and the largest splits, odd and unbalanced
+radices), band counts around a piece, several rows per tile, several spheres
+of different sizes, groups of planes, and the general kernels on the same
+inputs. Bars: those of the other parity tests."""
+import numpy as np
+import pytest
+
+import oracle
+import synth
+from gpu_util import TOL, check_workload, make_plan, rel, to_device
+
+pytestmark = pytest.mark.gpu
+
+# dims, k-points, bands
+SHAPES = [
+    ((16, 18, 20), 1, 3),       # one stage, then the shortest two-stage splits
+    ((18, 25, 27), 2, 1),       # odd radices, one band: many rows per tile
+    ((512, 4, 3), 1, 3),        # 32 x 16 along x (more bands are refused, as by the general kernels)
+    ((3, 512, 4), 1, 9),
+    ((4, 3, 512), 1, 8),
+    ((125, 6, 5), 1, 7),        # 25 x 5
+    ((5, 243, 6), 1, 2),        # 27 x 9
+    ((6, 5, 486), 1, 3),        # 27 x 18
+    ((48, 45, 64), 2, 37),      # ragged bands, several band tiles
+    ((60, 54, 50), 1, 16),
+]
+
+
+def _workload(dims, nk, nb, dtype, seed):
+    ks = np.random.default_rng(seed).uniform(-0.5, 0.5, (nk, 3))
+    semi = [max(0.25 * d, 0.6) for d in dims]
+    ks = [tuple(float(k) if d > 6 else 0.0 for k, d in zip(kk, dims)) for kk in ks]
+    return synth.small_workload(dims, semi, ks, nb, seed=seed, dtype=dtype, shuffle=True)
+
+
+@pytest.mark.parametrize("dtype", ["c128", "c64"])
+@pytest.mark.parametrize("i", range(len(SHAPES)))
+def test_pass_shapes(i, dtype, capfd, monkeypatch):
+    dims, nk, nb = SHAPES[i]
+    monkeypatch.setenv("FFTB_LOG", "1")
+    w = _workload(dims, nk, nb, dtype, 300 + i)
+    make_plan(w, dtype=dtype).close()
+    assert capfd.readouterr().err.count("axis passes") == 2
+    e = check_workload(w, dtype, flags=(0, 1, 4, 5)[i % 4], reps=2)
+    assert max(e) <= TOL[dtype], (dims, e)
+
+
+@pytest.mark.parametrize("dtype", ["c128", "c64"])
+@pytest.mark.parametrize("static", [False, True])
+def test_pass_groups_spheres_and_general_path(dtype, static, capfd, monkeypatch):
+    """Spheres with other maps and band counts in several groups of planes
+    (the bound makes the groups small), with the potential, against the oracle
+    and against the LDS-stage kernels."""
+    import torch
+    from paper_2406_05577_amd import Plan
+    dims, nbs = (30, 27, 20), [3, 11, 8]
+    ws = [synth.small_workload(dims, (7, 6, 5), [(0.1 * s, -0.2, 0.3)], nb, seed=50 + s, dtype=dtype,
+                               shuffle=True) for s, nb in enumerate(nbs)]
+    maps, coeffs = [w.spheres[0].lin for w in ws], [w.coeffs[0] for w in ws]
+    maps[1] = maps[1][: maps[1].shape[0] // 2]      # a sphere with missing columns
+    coeffs[1] = coeffs[1][: maps[1].shape[0]]
+    v = np.random.default_rng(5).standard_normal(dims[::-1]).astype("f8" if dtype == "c128" else "f4")
+    monkeypatch.setenv("FFTB_LOG", "1")
+    monkeypatch.setenv("FFTB_MAX_DEVICE_BYTES", str(1 << 30))
+    p = Plan(dims, maps, nbs, dtype=dtype)
+    assert "inverse: axis passes, 1 groups" not in capfd.readouterr().err
+    q = Plan(dims, maps, nbs, dtype=dtype, tuning=dict(path=1))
+    sph = to_device(np.concatenate([c.reshape(-1) for c in coeffs]), dtype)
+    vt = torch.from_numpy(v.reshape(-1)).cuda()
+    grid = torch.full((p.info["grid_elems"],), complex(float("nan"), 0.0), dtype=sph.dtype, device="cuda")
+    (p.sphere_to_grid_static if static else p.sphere_to_grid)(sph, grid)
+    plain = grid.clone()
+    out = p.apply_potential(sph, vt, grid=grid)
+    gq = q.sphere_to_grid(sph)
+    oq = q.apply_potential(sph, vt)
+    torch.cuda.synchronize()
+    assert rel(plain.cpu().numpy(), gq.cpu().numpy()) <= TOL[dtype]
+    assert rel(out.cpu().numpy(), oq.cpu().numpy()) <= TOL[dtype]
+    g, o, n = plain.cpu().numpy(), out.cpu().numpy(), dims[0] * dims[1] * dims[2]
+    ga = oa = 0
+    for m, c, nb in zip(maps, coeffs, nbs):
+        c = c.astype(np.complex128)
+        gg, oo = g[ga:ga + n * nb], o[oa:oa + c.size]
+        ga, oa = ga + n * nb, oa + c.size
+        assert rel(gg, oracle.sphere_to_grid(dims, m, c).ravel()) <= TOL[dtype]
+        assert rel(oo, oracle.apply_potential(dims, m, c, v.astype("f8")).ravel()) <= TOL[dtype]
+    p.close()
+    q.close()

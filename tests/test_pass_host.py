@@ -1,0 +1,72 @@
+"""CPU tests of the axis passes' host side: the tables, tiles and plane groups
+(walked as the kernel walks them, under the sanitizers), which plans take the
+passes, and what a device memory bound does to them. No GPU."""
+import os
+import re
+import shutil
+import subprocess
+
+import numpy as np
+import pytest
+
+import paper_2406_05577_amd as pk
+import synth
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+
+
+def test_pass_addresses_under_sanitizers(tmp_path):
+    gxx = shutil.which("g++")
+    if gxx is None:
+        pytest.skip("g++ not available")
+    exe = tmp_path / "pass_check"
+    csrc = os.path.join(ROOT, "paper_2406_05577_amd", "csrc")
+    subprocess.run([gxx, "-std=c++17", "-O1", "-g", "-fsanitize=address,undefined",
+                    "-fno-sanitize-recover=undefined",
+                    os.path.join(ROOT, "tests", "native", "pass_check.cpp"),
+                    os.path.join(csrc, "plan.cpp"), os.path.join(csrc, "pass_plan.cpp"),
+                    "-o", str(exe)], check=True)
+    res = subprocess.run([str(exe)], capture_output=True, text=True, timeout=120)
+    assert res.returncode == 0, res.stderr
+    assert "pass_check OK" in res.stdout
+
+
+def _log(capfd, dims, nb, dtype="c128", flags=0, tuning=None):
+    m, lin = synth.sphere_map(dims, [0.25 * d for d in dims], (0.1, 0.2, -0.3))
+    p = pk.Plan(dims, [lin], nb, dtype=dtype, flags=flags | pk.PLAN_HOST_ONLY, tuning=tuning)
+    return p, capfd.readouterr().err
+
+
+def test_which_plans_take_passes(monkeypatch, capfd):
+    """Passes: no tiling request and no band-inner x lines; every other plan
+    keeps the class-split kernels and reports their tiling."""
+    monkeypatch.setenv("FFTB_LOG", "1")
+    for dtype in ("c128", "c64"):
+        p, log = _log(capfd, (60, 50, 45), 7, dtype)
+        assert log.count("axis passes") == 2
+        # nothing to hand back but "the library's choice"
+        assert not any(v for d in ("inv", "fwd") for v in p.info["tuning"][d].values())
+        p, log = _log(capfd, (60, 50, 45), 7, dtype, tuning=dict(path=1))
+        assert "axis passes" not in log and p.info["tuning"]["inv"]["path"] == 1
+        p, log = _log(capfd, (60, 50, 45), 7, dtype, tuning=dict(inv_band_chunk=4))
+        assert log.count("inverse: axis passes") == 0 and log.count("forward: axis passes") == 1
+        # lines longer than any split, and band-inner shapes
+        _, log = _log(capfd, (6, 4, 540), 3, dtype)
+        assert "axis passes" not in log
+        p, log = _log(capfd, (96, 96, 96), 7, dtype)
+        assert p.info["tuning"]["inv"]["path"] == 3
+
+
+def test_pass_scratch_under_a_bound(monkeypatch, capfd):
+    """Under FFTB_MAX_DEVICE_BYTES the passes take no more scratch than the
+    class-split kernels did, in more groups of planes."""
+    monkeypatch.setenv("FFTB_LOG", "1")
+    _, log = _log(capfd, (60, 50, 45), 16)
+    assert "inverse: axis passes, 1 groups of 45 planes" in log
+    monkeypatch.setenv("FFTB_MAX_DEVICE_BYTES", str(1 << 30))
+    _, log = _log(capfd, (60, 50, 45), 16)
+    groups = int(re.search(r"inverse: axis passes, (\d+) groups", log).group(1))
+    assert groups > 1
+    scratch = float(re.search(r"scratch ([0-9.]+) GB", log).group(1))
+    _, log = _log(capfd, (60, 50, 45), 16, tuning=dict(path=1))
+    assert scratch <= float(re.search(r"scratch ([0-9.]+) GB", log).group(1))
