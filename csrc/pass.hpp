@@ -1,0 +1,95 @@
+// Axis passes: the transform as three kernels, one axis each, for every axis
+// length n = R1*R2 with codelets R1 and R2 (all 2,3,5-smooth lengths up to
+// 512). Shared by the host planner (pass_plan.cpp) and the kernels
+// (kernels_pass.hpp).
+#pragma once
+
+#include <cstdint>
+#include <string>
+#include <vector>
+
+#include "plan.hpp"
+
+namespace fftb {
+
+// ---- the split n = R1*R2 ---------------------------------------------------
+constexpr int kPassMaxN = 512;
+// in-register codelets the passes use
+constexpr bool pass_codelet(int r) {
+  return r == 1 || r == 2 || r == 3 || r == 4 || r == 5 || r == 6 || r == 8 || r == 9 || r == 10 ||
+         r == 12 || r == 15 || r == 16 || r == 18 || r == 20 || r == 24 || r == 25 || r == 27 ||
+         r == 32;
+}
+// First stage: one codelet up to 16, else the smallest codelet at or above the
+// root of n whose cofactor is a codelet too (the two stages then hold about
+// as many values per thread and keep about as many threads busy). 0: none.
+constexpr int pass_r1(int n) {
+  if (n <= 16 && pass_codelet(n)) return n;
+  for (int r = 2; r <= 32; ++r)
+    if (r * r >= n && n % r == 0 && pass_codelet(r) && pass_codelet(n / r)) return r;
+  return 0;
+}
+
+enum { kPassZ = 0, kPassY = 1, kPassX = 2 };
+
+// Per-sphere descriptor (device resident); offsets in complex elements (data)
+// or int32 entries (tables).
+struct PassSph {
+  int64_t sph_off, grid_off, col_off;
+  int64_t colrow;      // element stride between z planes of the column scratch
+  int32_t nb, ncol, nslab;
+  int32_t srow;        // element stride between y rows of a slab plane
+  int32_t gidx_off;    // ncol*nz: (column slot, z) -> coefficient or -1
+  int32_t colidx_off;  // nslab*ny: (slab, y) -> column slot or -1
+  int32_t xinv_off;    // nx: x -> slab or -1
+  int32_t ztile;       // first tile of the sphere in the z pass
+};
+
+struct PassArgs {
+  int kind;            // kPassZ / kPassY / kPassX
+  int nx, ny, nz, nsph;
+  int p0;              // y, x: first plane of the group (plane = sphere*nz + z)
+  int tiles;           // y, x: band tiles per plane / per row group
+  int rtiles;          // x: row groups per plane
+  int total;           // tiles of the launch
+  int fc, lines;       // a tile: fc elements of the fast dimension x `lines` rows (x)
+  int lds_tw;          // byte offset of the twiddle table in LDS
+  int nt_dense, nt_gather;  // streaming accesses on either side
+  int64_t splane;      // element stride between planes of the slab scratch
+  const PassSph* sph;
+  const int32_t* tab;  // gidx / colidx / xinv
+  const void *root, *root_lo;  // exp(-2*pi*i*j/n) (FP32: hi and lo)
+  const void* src;
+  void* dst;
+  const void* pot;     // x, inverse: real potential V[z][y][x] or null
+  double scale;        // z, forward: 1/N (1 elsewhere)
+};
+
+// ---- host side -------------------------------------------------------------
+struct PassTile {
+  int fc = 0, lines = 1, threads = 64;
+  int tiles = 0, rtiles = 0;
+  size_t lds = 0;
+  int lds_tw = 0;
+};
+
+struct PassPlan {
+  std::vector<PassSph> sph;
+  std::vector<int32_t> gidx, colidx, xinv;
+  PassTile tz, ty, tx;
+  int ztotal = 0;         // tiles of the z pass
+  int nplanes = 0;        // planes of all spheres
+  int group = 0;          // planes per y/x launch pair
+  int64_t splane = 0;     // slab scratch elements per plane
+  int64_t col_elems = 0;  // column scratch elements
+  int64_t s_elems() const { return splane * group; }
+};
+
+// Build the pass plan; false where a length has no split or a size does not
+// fit its index types. colrow_max: per sphere the most elements a z plane of
+// its columns may take (the padded row is used only within it); s_budget: the
+// most bytes the slab scratch of one group should take.
+bool build_pass_plan(int nx, int ny, int nz, bool fp64, const std::vector<SphereTables>& sph,
+                     const std::vector<int64_t>& colrow_max, int64_t s_budget, PassPlan& out);
+
+}  // namespace fftb

@@ -101,8 +101,9 @@ typedef struct {
 } fftb_sphere;
 
 /* Tiling of one direction. A zero field means "library default". With every
- * field zero the library may also choose axis passes (one kernel per axis, no
- * class split); such a direction reports all fields zero in fftb_plan_info. */
+ * field zero the library may run the direction as axis passes (one kernel per
+ * axis, no class split) where those are faster; fftb_plan_info then reports the
+ * class-split tiling that the direction would take otherwise. */
 typedef struct {
   int32_t band_chunk;   /* bands per workgroup tile, power of two, 1..64; path 3 takes one
                            128-byte piece (16 complex64 / 8 complex128 bands), and for the

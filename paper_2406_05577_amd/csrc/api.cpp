@@ -754,27 +754,43 @@ fftb_status choose_tiling(fftb_plan_s& P, int d, const fftb_dir_tuning& t) {
 }
 
 // Tiling of one direction: the class-split kernels' (which also decides what is
-// refused), and whether the direction runs as axis passes instead. Those take
-// every plan that asks for no tiling, has lines of at most 512 points and has no
-// band-inner x shape: its class-split kernels would be the LDS-stage or the
-// register ones, which re-read or re-transform per y class (round trips, class
-// split -> passes: 108x100x120, 50 complex64 bands, 7.50 -> 0.68 ms;
-// 200x192x216, 20 complex128 bands, 87.4 -> 2.69 ms; 256^3, 24 complex128 bands
-// on register lines, 10.8 -> 6.69 ms).
+// refused), and whether the direction runs as axis passes instead. Plans that ask
+// for no tiling and have lines of at most 512 points take passes
+// - where x has no band-inner shape: the class-split kernels would be the
+//   LDS-stage or the register ones, which re-read or re-transform per y class
+//   (round trips, class split -> passes: 108x100x120, 50 complex64 bands, 7.50 ->
+//   0.59 ms; 200x192x216, 20 complex128 bands, 87.4 -> 2.34 ms; 256^3, 24
+//   complex128 bands on register lines, 10.8 -> 5.45 ms);
+// - forward: the class partials make a round trip through HBM where the slab
+//   scratch of a plane group stays in the last-level cache (144x160x180, 128
+//   complex128 bands: 4.41 -> 3.55 ms; 96^3, 8 x 64 complex64 bands: 1.83 -> 1.62
+//   ms; 128^3, 256 complex64 bands: 2.17 -> 1.98 ms);
+// - inverse with too few plane tasks to fill the 256 CUs (32^3, 4 complex128
+//   bands, 32 tasks: 23 -> 17 us; with 512 tasks, 256 complex64 bands, the class
+//   pairs are faster: 39 against 45 us, as they are on every larger grid:
+//   144x160x180 3.28 against 3.61 ms).
 fftb_status choose_dir(fftb_plan_s& P, int d, const fftb_dir_tuning& t) {
   DirCfg& D = P.dir[d];
   D.pass = false;
   const fftb_status st = choose_tiling(P, d, t);
   if (st != FFTB_OK) return st;
   const fftb_dir_tuning none = {};
-  D.pass = std::memcmp(&t, &none, sizeof t) == 0 && !D.bil2 && !(P.flags & FFTB_PLAN_MFMA) &&
-           P.nx <= kPassMaxN && P.ny <= kPassMaxN && P.nz <= kPassMaxN;
+  if (std::memcmp(&t, &none, sizeof t) != 0 || (P.flags & FFTB_PLAN_MFMA) || P.nx > kPassMaxN ||
+      P.ny > kPassMaxN || P.nz > kPassMaxN)
+    return FFTB_OK;
+  int64_t tasks = 0;
+  for (const auto& s : P.sph)
+    tasks += static_cast<int64_t>(P.nz) * ((s.nb + D.bc - 1) / D.bc) * (D.n1 / D.qc);
+  D.pass = !D.bil2 || d == 1 || tasks < 256;
   return FFTB_OK;
 }
 
 // Slab scratch of one y/x group: what stays in the 256 MB last-level cache
-// between the two passes beside the grid's stream (streamed past it).
-constexpr int64_t kSlabBudget = int64_t{128} << 20;
+// between the two passes, the grid being streamed past it. Larger groups have
+// fewer launches with empty CUs at their ends (256^3, 24 complex128 bands, a
+// round trip with 64, 128, 192, 224 MB: 6.80, 5.86, 5.58, 5.45 ms; the whole
+// scratch at once: 6.19 ms).
+constexpr int64_t kSlabBudget = int64_t{224} << 20;
 
 // Build the pass plan of the directions that chose passes; they fall back to
 // the class-split kernels where it does not fit.
@@ -1306,6 +1322,7 @@ hipError_t enqueue_pass(fftb_plan_s* P, const void* in, void* out, bool inverse,
     a.fc = t.fc;
     a.lines = t.lines;
     a.lds_tw = t.lds_tw;
+    a.group = t.group;
     const void* gat;  // the side reached through the table, and the dense side
     const void* den;
     int n;
@@ -1452,18 +1469,6 @@ void log_plan(const fftb_plan_s& P) {
                static_cast<double>(P.scratch_elems()) * es_of(P.dtype) / 1e9);
   for (int d = 0; d < 2; ++d) {
     const DirCfg& D = P.dir[d];
-    if (D.pass) {
-      std::fprintf(stderr, "  %s: axis passes, %d groups of %d planes", d == 0 ? "inverse" : "forward",
-                   (P.pp.nplanes + P.pp.group - 1) / P.pp.group, P.pp.group);
-      const char* name[3] = {"z", "y", "x"};
-      const PassTile* tl[3] = {&P.pp.tz, &P.pp.ty, &P.pp.tx};
-      const int n[3] = {P.nz, P.ny, P.nx};
-      for (int i = 0; i < 3; ++i)
-        std::fprintf(stderr, ", %s %dx%d tile %d elements x %d rows, %d threads, LDS %zu B", name[i],
-                     pass_r1(n[i]), n[i] / pass_r1(n[i]), tl[i]->fc, tl[i]->lines, tl[i]->threads, tl[i]->lds);
-      std::fprintf(stderr, "\n");
-      continue;
-    }
     std::fprintf(stderr,
                  "  %s: band chunk %d, %d y classes of %d, %d threads, column kernel %s (%dx%d, %d "
                  "columns/task, %d tasks), plane kernel %s (%dx%d, LDS %zu B, %d tasks)%s%s, "
@@ -1475,6 +1480,18 @@ void log_plan(const fftb_plan_s& P) {
                  D.fwd_cls ? ", class partials + combine" : D.qc == 2 ? ", class pairs" : "",
                  D.mf2 || D.mf1 ? ", matrix-core DFT_16" : "",
                  D.fold_m);
+    // the axis passes the direction takes instead
+    if (D.pass) {
+      std::fprintf(stderr, "  %s: axis passes, %d groups of %d planes", d == 0 ? "inverse" : "forward",
+                   (P.pp.nplanes + P.pp.group - 1) / P.pp.group, P.pp.group);
+      const char* name[3] = {"z", "y", "x"};
+      const PassTile* tl[3] = {&P.pp.tz, &P.pp.ty, &P.pp.tx};
+      const int n[3] = {P.nz, P.ny, P.nx};
+      for (int i = 0; i < 3; ++i)
+        std::fprintf(stderr, ", %s %dx%d tile %d elements x %d rows, %d threads, LDS %zu B", name[i],
+                     pass_r1(n[i]), n[i] / pass_r1(n[i]), tl[i]->fc, tl[i]->lines, tl[i]->threads, tl[i]->lds);
+      std::fprintf(stderr, "\n");
+    }
   }
 }
 
@@ -1838,7 +1855,6 @@ fftb_status fftb_plan_create(fftb_plan* out, const int32_t dims[3], const fftb_s
     for (int d = 0; d < 2; ++d) {
       const DirCfg& D = P->dir[d];
       fftb_dir_tuning& o = d == 0 ? P->tun.inv : P->tun.fwd;
-      if (D.pass) continue;  // no class-split tiling in use: all zero
       o.band_chunk = D.narrow ? D.bc2 : D.bc;
       o.y_classes = D.n1;
       o.x_rows = D.lx;

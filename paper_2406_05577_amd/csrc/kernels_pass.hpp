@@ -18,12 +18,14 @@
 // so that the rows a wave reads together start in other banks.
 //
 // Bound by memory: a pass reads and writes each value once (2.4 flop per byte
-// moved at 200 points). The y and x passes run over groups of planes whose
-// slab scratch (128 MB) stays in the last-level cache between the two, with the
-// grid streamed past it: a copy of that shape moved 6.7 TB/s, against 4.5 TB/s
-// over the whole scratch at once. At 200x192x216, 20 complex128 bands, a round
-// trip takes 2.69 ms (2.1 TB/s of sphere and grid; 87 ms on the LDS-stage
-// kernels).
+// moved at 200 points), with enough workgroups in flight: the exchange sends the
+// real and the imaginary parts one after the other, half the LDS for two more
+// barriers (144x160x180, 128 complex128 bands, a round trip: 8.80 -> 7.80 ms).
+// The y and x passes run over groups of planes whose slab scratch stays in the
+// last-level cache between the two, with the grid streamed past it
+// (non-temporal): a copy of that shape moved 6.7 TB/s, against 4.5 TB/s over the
+// whole scratch at once. At 200x192x216, 20 complex128 bands, the x passes move
+// 5.6 TB/s and a round trip takes 2.34 ms (87 ms on the LDS-stage kernels).
 #pragma once
 
 #include "bline.hpp"
@@ -32,18 +34,33 @@
 
 namespace fftb {
 
-template <typename T>
-__device__ __forceinline__ cpx<T> ld_c(const cpx<T>* p, bool nt) {
+template <bool NT, typename T>
+__device__ __forceinline__ cpx<T> ld_c(const cpx<T>* p) {
   typedef T v2 __attribute__((ext_vector_type(2)));
-  const v2 x = nt ? __builtin_nontemporal_load(reinterpret_cast<const v2*>(p))
-                  : *reinterpret_cast<const v2*>(p);
+  v2 x;
+  if constexpr (NT) x = __builtin_nontemporal_load(reinterpret_cast<const v2*>(p));
+  else x = *reinterpret_cast<const v2*>(p);
   return {x.x, x.y};
 }
-template <typename T>
-__device__ __forceinline__ void st_c(cpx<T>* p, cpx<T> v, bool nt) {
+template <bool NT, typename T>
+__device__ __forceinline__ void st_c(cpx<T>* p, cpx<T> v) {
   typedef T v2 __attribute__((ext_vector_type(2)));
-  if (nt) __builtin_nontemporal_store(v2{v.re, v.im}, reinterpret_cast<v2*>(p));
+  if constexpr (NT) __builtin_nontemporal_store(v2{v.re, v.im}, reinterpret_cast<v2*>(p));
   else *reinterpret_cast<v2*>(p) = v2{v.re, v.im};
+}
+// Run f with the uniform flag nt as a constant. The fences keep the compiler
+// from merging the two copies, which would drop the non-temporal hint.
+template <class F>
+__device__ __forceinline__ void with_nt(bool nt, F&& f) {
+  if (nt) {
+    asm volatile("; streaming" ::: "memory");
+    f(std::true_type{});
+    asm volatile("; end streaming" ::: "memory");
+  } else {
+    asm volatile("; cached" ::: "memory");
+    f(std::false_type{});
+    asm volatile("; end cached" ::: "memory");
+  }
 }
 
 // floor(n / d) for 0 <= n < 2^22 through a float reciprocal and one correction
@@ -55,14 +72,15 @@ __device__ __forceinline__ int pass_div(int n, int d, float inv_d) {
 }
 
 template <int S, typename T, int N>
-__global__ void __launch_bounds__(512) pass_kernel(const PassArgs a) {
+__global__ void __launch_bounds__(pass_max_threads(N, sizeof(T) == 8)) pass_kernel(const PassArgs a) {
   constexpr int R1 = pass_r1(N), R2 = N / R1, RS = R2 | 1;
   extern __shared__ __align__(16) unsigned char smem_raw[];
-  cpx<T>* buf = reinterpret_cast<cpx<T>*>(smem_raw);
+  T* buf = reinterpret_cast<T*>(smem_raw);
   TwEntry<T>* tw = reinterpret_cast<TwEntry<T>*>(smem_raw + a.lds_tw);
 
   // the tile: sphere, first element f0 of nf, rows, and the two sides' bases
-  const int t = blockIdx.x;
+  const int t = static_task_g(a.total, a.group);
+  if (t < 0) return;
   int s = 0, f0, nf, nl = 1, trow = N;
   const int32_t* __restrict__ tab = a.tab;
   const cpx<T>* src = reinterpret_cast<const cpx<T>*>(a.src);
@@ -132,14 +150,19 @@ __global__ void __launch_bounds__(512) pass_kernel(const PassArgs a) {
       int g[R1];
 #pragma unroll
       for (int q = 0; q < R1; ++q) g[q] = ok ? row[R2 * q] : -1;
+      with_nt(ntg, [&](auto nt) {
 #pragma unroll
-      for (int q = 0; q < R1; ++q)
-        v[q] = g[q] >= 0 ? ld_c(base + static_cast<int64_t>(g[q]) * nb, ntg) : cpx<T>{0, 0};
+        for (int q = 0; q < R1; ++q)
+          v[q] = g[q] >= 0 ? ld_c<decltype(nt)::value>(base + static_cast<int64_t>(g[q]) * nb)
+                           : cpx<T>{0, 0};
+      });
     } else {
       const cpx<T>* base = dsrc + f + i * pstride + static_cast<int64_t>(l) * dstep;
+      with_nt(ntd, [&](auto nt) {
 #pragma unroll
-      for (int q = 0; q < R1; ++q)
-        v[q] = ok ? ld_c(base + (R2 * q) * pstride, ntd) : cpx<T>{0, 0};
+        for (int q = 0; q < R1; ++q)
+          v[q] = ok ? ld_c<decltype(nt)::value>(base + (R2 * q) * pstride) : cpx<T>{0, 0};
+      });
     }
   };
   // stage 2 (or the only stage): thread (f, k1, l) writes positions k1 + R1*k2
@@ -153,8 +176,10 @@ __global__ void __launch_bounds__(512) pass_kernel(const PassArgs a) {
         for (int k = 0; k < CT; ++k) u[k] = cscale(u[k], vr[ST * k]);
       }
       cpx<T>* base = ddst + f + k1 * pstride + static_cast<int64_t>(l) * dstep;
+      with_nt(ntd, [&](auto nt) {
 #pragma unroll
-      for (int k = 0; k < CT; ++k) st_c(base + (ST * k) * pstride, u[k], ntd);
+        for (int k = 0; k < CT; ++k) st_c<decltype(nt)::value>(base + (ST * k) * pstride, u[k]);
+      });
     } else {
       const int bb = b0 + f;
       const int dc = pass_div(bb, nb, inv_nb);
@@ -164,9 +189,11 @@ __global__ void __launch_bounds__(512) pass_kernel(const PassArgs a) {
       int g[CT];
 #pragma unroll
       for (int k = 0; k < CT; ++k) g[k] = row[ST * k];
+      with_nt(ntg, [&](auto nt) {
 #pragma unroll
-      for (int k = 0; k < CT; ++k)
-        if (g[k] >= 0) st_c(base + static_cast<int64_t>(g[k]) * nb, cscale(u[k], sc), ntg);
+        for (int k = 0; k < CT; ++k)
+          if (g[k] >= 0) st_c<decltype(nt)::value>(base + static_cast<int64_t>(g[k]) * nb, cscale(u[k], sc));
+      });
     }
   };
 
@@ -179,40 +206,53 @@ __global__ void __launch_bounds__(512) pass_kernel(const PassArgs a) {
     }
     return;
   } else {
-    int it = threadIdx.x;
-    if (it < items1) load(it);
+    // (the host gives every item of either stage its own thread)
+    const int it = threadIdx.x;
+    const bool on1 = it < items1;
+    if (on1) load(it);
     bl_fill_twiddles<S, T>(tw, reinterpret_cast<const cpx<T>*>(a.root),
                            reinterpret_cast<const cpx<T>*>(a.root_lo), R1, R2);
     __syncthreads();
-    while (it < items1) {
-      const int rest = pass_div(it, fc, inv_fc);
-      const int f = it - rest * fc, l = rest / R2, i = rest - l * R2;
+    const int rest1 = pass_div(it, fc, inv_fc);
+    const int f = it - rest1 * fc;
+    const int l1 = rest1 / R2, i1 = rest1 - l1 * R2;
+    const int l2 = rest1 / R1, k1 = rest1 - l2 * R1;
+    const bool on2 = it < a.lines * R1 * fc;
+    if (on1) {
       dft<R1, S>(v);
-      const TwEntry<T>* tr = tw + i * tw_row_stride(R1);
-      cpx<T>* out = buf + (l * R1 * RS + i) * fc + f;
-      out[0] = v[0];
+      const TwEntry<T>* tr = tw + i1 * tw_row_stride(R1);
 #pragma unroll
       for (int k = 1; k < R1; ++k) {
         const TwEntry<T> w = tr[k];
         if constexpr (std::is_same<T, float>::value)
-          out[k * RS * fc] = cmul_hl(v[k], cpx<float>{w.re, w.im}, cpx<float>{w.lre, w.lim});
+          v[k] = cmul_hl(v[k], cpx<float>{w.re, w.im}, cpx<float>{w.lre, w.lim});
         else
-          out[k * RS * fc] = cmul(v[k], cpx<double>{w.re, w.im});
+          v[k] = cmul(v[k], cpx<double>{w.re, w.im});
       }
-      it += blockDim.x;
-      if (it < items1) load(it);
+    }
+    T* out = buf + (l1 * R1 * RS + i1) * fc + f;
+    const T* in = buf + (l2 * R1 + k1) * RS * fc + f;
+    cpx<T> u[R2];
+    if (on1) {
+#pragma unroll
+      for (int k = 0; k < R1; ++k) out[k * RS * fc] = v[k].re;
     }
     __syncthreads();
-    const int items2 = a.lines * R1 * fc;
-    for (int j = threadIdx.x; j < items2; j += blockDim.x) {
-      const int rest = pass_div(j, fc, inv_fc);
-      const int f = j - rest * fc, l = rest / R1, k1 = rest - l * R1;
-      const cpx<T>* in = buf + (l * R1 + k1) * RS * fc + f;
-      cpx<T> u[R2];
+    if (on2) {
 #pragma unroll
-      for (int i = 0; i < R2; ++i) u[i] = in[i * fc];
+      for (int i = 0; i < R2; ++i) u[i].re = in[i * fc];
+    }
+    __syncthreads();
+    if (on1) {
+#pragma unroll
+      for (int k = 0; k < R1; ++k) out[k * RS * fc] = v[k].im;
+    }
+    __syncthreads();
+    if (on2) {
+#pragma unroll
+      for (int i = 0; i < R2; ++i) u[i].im = in[i * fc];
       dft<R2, S>(u);
-      emit(f, l, k1, u, std::integral_constant<int, R1>{}, std::integral_constant<int, R2>{});
+      emit(f, l2, k1, u, std::integral_constant<int, R1>{}, std::integral_constant<int, R2>{});
     }
   }
 }
@@ -234,7 +274,7 @@ hipError_t pass_one(const PassArgs& a, int threads, size_t lds, hipStream_t st, 
   if (attr_only)
     return hipFuncSetAttribute(reinterpret_cast<const void*>(pass_kernel<S, T, N>),
                                hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(lds));
-  hipLaunchKernelGGL((pass_kernel<S, T, N>), dim3(a.total), dim3(threads), lds, st, a);
+  hipLaunchKernelGGL((pass_kernel<S, T, N>), dim3(pass_grid(a.total, a.group)), dim3(threads), lds, st, a);
   return hipGetLastError();
 }
 

@@ -30,6 +30,16 @@ constexpr int pass_r1(int n) {
   return 0;
 }
 
+// Threads per workgroup the kernels are compiled for (FP64 lines of longer
+// codelets need more than the 128 registers that 1024 threads leave).
+constexpr int pass_max_threads(int n, bool fp64) {
+  return !fp64 || pass_r1(n) <= 12 ? 1024 : 512;
+}
+// Blocks of a launch whose tiles go to the XCDs in runs of `group`.
+constexpr int pass_grid(int total, int group) {
+  return (total + 8 * group - 1) / (8 * group) * (8 * group);
+}
+
 enum { kPassZ = 0, kPassY = 1, kPassX = 2 };
 
 // Per-sphere descriptor (device resident); offsets in complex elements (data)
@@ -52,6 +62,7 @@ struct PassArgs {
   int tiles;           // y, x: band tiles per plane / per row group
   int rtiles;          // x: row groups per plane
   int total;           // tiles of the launch
+  int group;           // consecutive tiles that run on one XCD
   int fc, lines;       // a tile: fc elements of the fast dimension x `lines` rows (x)
   int lds_tw;          // byte offset of the twiddle table in LDS
   int nt_dense, nt_gather;  // streaming accesses on either side
@@ -69,6 +80,7 @@ struct PassArgs {
 struct PassTile {
   int fc = 0, lines = 1, threads = 64;
   int tiles = 0, rtiles = 0;
+  int group = 1;  // consecutive tiles that share an XCD
   size_t lds = 0;
   int lds_tw = 0;
 };

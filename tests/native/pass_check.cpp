@@ -39,7 +39,7 @@ static void walk(const PassPlan& P, int kind, int nx, int ny, int nz, int p0, in
   const int r1 = pass_r1(n), r2 = n / r1;
   const int total = kind == kPassZ ? P.ztotal : kind == kPassY ? np * t.tiles : np * t.tiles * t.rtiles;
   const std::vector<int32_t>& table = kind == kPassZ ? P.gidx : kind == kPassY ? P.colidx : P.xinv;
-  CHECK(t.threads >= 64 && t.threads <= 512 && t.threads % 64 == 0);
+  CHECK(t.threads >= 64 && t.threads % 64 == 0);
   CHECK(t.lds_tw + (r2 > 1 ? (r1 | 1) * r2 * 16 : 0) <= static_cast<int>(t.lds));
   for (int b = 0; b < total; ++b) {
     size_t s = 0;

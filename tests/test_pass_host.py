@@ -38,14 +38,12 @@ def _log(capfd, dims, nb, dtype="c128", flags=0, tuning=None):
 
 
 def test_which_plans_take_passes(monkeypatch, capfd):
-    """Passes: no tiling request and no band-inner x lines; every other plan
-    keeps the class-split kernels and reports their tiling."""
+    """Passes: no tiling request, and no band-inner x lines, the forward, or too
+    few inverse tasks; every other direction keeps the class-split kernels."""
     monkeypatch.setenv("FFTB_LOG", "1")
     for dtype in ("c128", "c64"):
         p, log = _log(capfd, (60, 50, 45), 7, dtype)
         assert log.count("axis passes") == 2
-        # nothing to hand back but "the library's choice"
-        assert not any(v for d in ("inv", "fwd") for v in p.info["tuning"][d].values())
         p, log = _log(capfd, (60, 50, 45), 7, dtype, tuning=dict(path=1))
         assert "axis passes" not in log and p.info["tuning"]["inv"]["path"] == 1
         p, log = _log(capfd, (60, 50, 45), 7, dtype, tuning=dict(inv_band_chunk=4))
@@ -53,8 +51,14 @@ def test_which_plans_take_passes(monkeypatch, capfd):
         # lines longer than any split, and band-inner shapes
         _, log = _log(capfd, (6, 4, 540), 3, dtype)
         assert "axis passes" not in log
+        # band-inner shapes: the forward, and an inverse of fewer tasks than CUs
         p, log = _log(capfd, (96, 96, 96), 7, dtype)
-        assert p.info["tuning"]["inv"]["path"] == 3
+        assert p.info["tuning"]["inv"]["path"] == 3 and "forward: axis passes" in log
+        assert "inverse: axis passes" not in log
+        _, log = _log(capfd, (32, 32, 32), 7, dtype)
+        assert log.count("axis passes") == 2
+        _, log = _log(capfd, (96, 96, 96), 7, dtype, tuning=dict(path=3))
+        assert "axis passes" not in log
 
 
 def test_pass_scratch_under_a_bound(monkeypatch, capfd):
