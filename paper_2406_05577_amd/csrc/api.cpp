@@ -42,9 +42,9 @@ hipError_t launch_bil(int which, const KArgs& a, bool inverse, bool fp64, int E,
                       int threads, size_t lds, hipStream_t st, int fold_m);
 hipError_t prepare_bil(bool fp64, int E, int H, size_t lds, bool narrow);
 hipError_t launch_zero_scratch(void* p, size_t bytes, hipStream_t st);
-hipError_t launch_pass(bool inverse, bool fp64, int n, const PassArgs& a, int threads, size_t lds,
+hipError_t launch_pass(bool inverse, PassElem el, int n, const PassArgs& a, int threads, size_t lds,
                        hipStream_t st);
-hipError_t prepare_pass(bool inverse, bool fp64, int n, size_t lds);
+hipError_t prepare_pass(bool inverse, PassElem el, int n, size_t lds);
 }  // namespace fftb
 
 using namespace fftb;
@@ -1095,7 +1095,7 @@ fftb_status device_setup(fftb_plan_s& P, hipStream_t st) {
       size_t lds = tl[i]->lds;  // axes of one length share the kernel
       for (int j = 0; j < 3; ++j)
         if (n[j] == n[i]) lds = std::max(lds, tl[j]->lds);
-      e = prepare_pass(d == 0, fp64, n[i], lds);
+      e = prepare_pass(d == 0, P.pp.elem, n[i], lds);
       if (e != hipSuccess)
         return fail(FFTB_ERR_HIP, std::string("hipFuncSetAttribute: ") + hipGetErrorString(e));
     }
@@ -1300,7 +1300,6 @@ hipError_t enqueue(fftb_plan_s* P, const KArgs& a, const DirCfg& D, bool inverse
 // cache between them. The two together take the profile slot of the plane kernel.
 hipError_t enqueue_pass(fftb_plan_s* P, const void* in, void* out, bool inverse, const void* pot,
                         void* col, hipStream_t st, bool profile) {
-  const bool fp64 = P->dtype == FFTB_C128;
   const PassPlan& pp = P->pp;
   const size_t es = static_cast<size_t>(es_of(P->dtype));
   void* slab = static_cast<char*>(P->d_col) + static_cast<size_t>(P->pass_at + pp.col_elems) * es;
@@ -1322,6 +1321,8 @@ hipError_t enqueue_pass(fftb_plan_s* P, const void* in, void* out, bool inverse,
     a.fc = t.fc;
     a.lines = t.lines;
     a.lds_tw = t.lds_tw;
+    a.lds_tab = t.lds_tab;
+    a.tab_lds = t.tab_lds ? 1 : 0;
     a.group = t.group;
     const void* gat;  // the side reached through the table, and the dense side
     const void* den;
@@ -1357,7 +1358,7 @@ hipError_t enqueue_pass(fftb_plan_s* P, const void* in, void* out, bool inverse,
     }
     a.src = inverse ? gat : den;
     a.dst = const_cast<void*>(inverse ? den : gat);
-    return launch_pass(inverse, fp64, n, a, t.threads, t.lds, st);
+    return launch_pass(inverse, pp.elem, n, a, t.threads, t.lds, st);
   };
   auto timed = [&](int kid, auto&& body) {
     hipEvent_t ea = nullptr, eb = nullptr;

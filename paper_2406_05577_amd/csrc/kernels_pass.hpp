@@ -12,10 +12,13 @@
 // takes fc consecutive elements of the flattened (line, band) dimension (for
 // x: of the bands, and several rows where the bands are few).
 //
-// Each thread holds R1, then R2, values of one line: DFT_R1 over stride R2,
-// twiddles w_n^{i*k} from a table in LDS, an exchange through LDS, DFT_R2
-// (Section 2.1). The rows of the exchange are an odd number of pieces apart
-// so that the rows a wave reads together start in other banks.
+// Each thread holds R1, then R2, values of one line (complex64: of two
+// neighbouring bands, 16 bytes per lane): DFT_R1 over stride R2, twiddles
+// w_n^{i*k} from a table in LDS, an exchange through LDS, DFT_R2 (Section 2.1).
+// The rows of the exchange are an odd number of pieces apart so that the rows a
+// wave reads together start in other banks. The tile's table rows are staged in
+// LDS as byte offsets where they are few: one coalesced load in the place of R1
+// loads per thread, and buffer accesses that need no branch for absent entries.
 //
 // Bound by memory: a pass reads and writes each value once (2.4 flop per byte
 // moved at 200 points), with enough workgroups in flight: the exchange sends the
@@ -24,8 +27,12 @@
 // The y and x passes run over groups of planes whose slab scratch stays in the
 // last-level cache between the two, with the grid streamed past it
 // (non-temporal): a copy of that shape moved 6.7 TB/s, against 4.5 TB/s over the
-// whole scratch at once. At 200x192x216, 20 complex128 bands, the x passes move
-// 5.6 TB/s and a round trip takes 2.34 ms (87 ms on the LDS-stage kernels).
+// whole scratch at once. At 144^3, 96 complex64 bands, the inverse x, y and z
+// passes move 6.1, 5.6 and 5.3 TB/s. One complex64 band per lane, no staged
+// tables -> two and staged: 128^3, 256 complex64 bands, forward 1.95 -> 1.79 ms;
+// 108x100x120, 50 bands, a round trip 0.58 -> 0.50 ms; complex128 (staged tables
+// only) 144x160x180, 128 bands, 7.08 -> 6.85 ms. At 200x192x216, 20 complex128
+// bands, a round trip takes 2.32 ms (87 ms on the LDS-stage kernels).
 #pragma once
 
 #include "bline.hpp"
@@ -34,19 +41,74 @@
 
 namespace fftb {
 
-template <bool NT, typename T>
-__device__ __forceinline__ cpx<T> ld_c(const cpx<T>* p) {
-  typedef T v2 __attribute__((ext_vector_type(2)));
-  v2 x;
-  if constexpr (NT) x = __builtin_nontemporal_load(reinterpret_cast<const v2*>(p));
-  else x = *reinterpret_cast<const v2*>(p);
-  return {x.x, x.y};
+// One element of a lane: V neighbouring bands (16 bytes: one complex128 or two
+// complex64 values, or 8 bytes), at any address that a value may have.
+template <typename T, int V>
+struct ElemVec {
+  typedef T type __attribute__((ext_vector_type(2 * V), aligned(8)));
+  // what stores write
+  typedef int words __attribute__((ext_vector_type(V * sizeof(T) / 2), aligned(8)));
+};
+template <typename T, int V>
+struct Elem {
+  cpx<T> a, b;  // (b: V == 2)
+};
+template <int V, typename T, typename E>
+__device__ __forceinline__ Elem<T, V> unpack(E x) {
+  if constexpr (V == 1) return {{x.x, x.y}, {0, 0}};
+  else return {{x.x, x.y}, {x.z, x.w}};
 }
-template <bool NT, typename T>
-__device__ __forceinline__ void st_c(cpx<T>* p, cpx<T> v) {
-  typedef T v2 __attribute__((ext_vector_type(2)));
-  if constexpr (NT) __builtin_nontemporal_store(v2{v.re, v.im}, reinterpret_cast<v2*>(p));
-  else *reinterpret_cast<v2*>(p) = v2{v.re, v.im};
+template <int V, typename T>
+__device__ __forceinline__ typename ElemVec<T, V>::words pack(T ar, T ai, T br, T bi) {
+  if constexpr (std::is_same<T, double>::value) {
+    const long long re = __double_as_longlong(ar), im = __double_as_longlong(ai);
+    return {static_cast<int>(re), static_cast<int>(re >> 32), static_cast<int>(im), static_cast<int>(im >> 32)};
+  } else if constexpr (V == 1) {
+    return {__float_as_int(ar), __float_as_int(ai)};
+  } else {
+    // (opaque: the compiler would read ar and ai back from their array as one
+    // wide load, which keeps the array in scratch memory)
+    asm("" : "+v"(ar));
+    return {__float_as_int(ar), __float_as_int(ai), __float_as_int(br), __float_as_int(bi)};
+  }
+}
+template <bool NT, int V, typename T>
+__device__ __forceinline__ Elem<T, V> ld_el(const cpx<T>* p) {
+  using E = typename ElemVec<T, V>::type;
+  if constexpr (NT) return unpack<V, T>(__builtin_nontemporal_load(reinterpret_cast<const E*>(p)));
+  else return unpack<V, T>(*reinterpret_cast<const E*>(p));
+}
+template <bool NT, int V, typename T>
+__device__ __forceinline__ void st_el(cpx<T>* p, T ar, T ai, T br, T bi) {
+  using E = typename ElemVec<T, V>::words;
+  if constexpr (NT) __builtin_nontemporal_store(pack<V>(ar, ai, br, bi), reinterpret_cast<E*>(p));
+  else *reinterpret_cast<E*>(p) = pack<V>(ar, ai, br, bi);
+}
+// The same through a buffer of 2 GiB: an offset at or past its end reads zero
+// and stores nothing, so absent table entries need no branch.
+constexpr unsigned kPassAbsent = 0x80000000u;
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t pass_rsrc(const void* base) {
+  const uint64_t pa = reinterpret_cast<uint64_t>(base);
+  const uint32_t lo = __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(pa));
+  const uint32_t hi = __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(pa >> 32));
+  void* p = reinterpret_cast<void*>((static_cast<uint64_t>(hi) << 32) | lo);
+  return __builtin_amdgcn_make_buffer_rsrc(p, static_cast<short>(0), static_cast<int>(kPassAbsent),
+                                           0x00020000);
+}
+template <bool NT, int V, typename T>
+__device__ __forceinline__ Elem<T, V> buf_ld_el(__amdgpu_buffer_rsrc_t r, unsigned off, unsigned soff) {
+  typedef T E __attribute__((ext_vector_type(2 * V)));
+  if constexpr (sizeof(E) == 16)
+    return unpack<V, T>(__builtin_bit_cast(E, __builtin_amdgcn_raw_buffer_load_b128(r, off, soff, NT ? 2 : 0)));
+  else
+    return unpack<V, T>(__builtin_bit_cast(E, __builtin_amdgcn_raw_buffer_load_b64(r, off, soff, NT ? 2 : 0)));
+}
+template <bool NT, int V, typename T>
+__device__ __forceinline__ void buf_st_el(__amdgpu_buffer_rsrc_t r, T ar, T ai, T br, T bi, unsigned off,
+                                          unsigned soff) {
+  const typename ElemVec<T, V>::words x = pack<V>(ar, ai, br, bi);
+  if constexpr (sizeof(x) == 16) __builtin_amdgcn_raw_buffer_store_b128(x, r, off, soff, NT ? 2 : 0);
+  else __builtin_amdgcn_raw_buffer_store_b64(x, r, off, soff, NT ? 2 : 0);
 }
 // Run f with the uniform flag nt as a constant. The fences keep the compiler
 // from merging the two copies, which would drop the non-temporal hint.
@@ -71,12 +133,15 @@ __device__ __forceinline__ int pass_div(int n, int d, float inv_d) {
   return q;
 }
 
-template <int S, typename T, int N>
-__global__ void __launch_bounds__(pass_max_threads(N, sizeof(T) == 8)) pass_kernel(const PassArgs a) {
+template <int S, typename T, int V, int N>
+__global__ void __launch_bounds__(pass_max_threads(N, sizeof(T) * V == 4)) pass_kernel(const PassArgs a) {
   constexpr int R1 = pass_r1(N), R2 = N / R1, RS = R2 | 1;
+  constexpr unsigned es = sizeof(cpx<T>);
+  typedef T Part __attribute__((ext_vector_type(V)));  // the real or imaginary parts of an element
   extern __shared__ __align__(16) unsigned char smem_raw[];
-  T* buf = reinterpret_cast<T*>(smem_raw);
+  Part* buf = reinterpret_cast<Part*>(smem_raw);
   TwEntry<T>* tw = reinterpret_cast<TwEntry<T>*>(smem_raw + a.lds_tw);
+  unsigned* ltab = reinterpret_cast<unsigned*>(smem_raw + a.lds_tab);
 
   // the tile: sphere, first element f0 of nf, rows, and the two sides' bases
   const int t = static_task_g(a.total, a.group);
@@ -86,26 +151,31 @@ __global__ void __launch_bounds__(pass_max_threads(N, sizeof(T) == 8)) pass_kern
   const cpx<T>* src = reinterpret_cast<const cpx<T>*>(a.src);
   cpx<T>* dst = reinterpret_cast<cpx<T>*>(a.dst);
   int64_t gat, den, pstride, vrow = 0;
-  int gstep = 0, dstep = 0;
+  int gstep = 0, dstep = 0, gnb, dnb;  // row steps, band strides of the two sides
+  bool tail_g = false, tail_d = false;  // sides whose band vectors may end in half an element
   if (a.kind == kPassZ) {
     while (s + 1 < a.nsph && t >= a.sph[s + 1].ztile) ++s;
-    const PassSph d = a.sph[s];
+  } else {
+    s = (a.p0 + (a.kind == kPassX ? t / (a.tiles * a.rtiles) : t / a.tiles)) / a.nz;
+  }
+  const PassSph d = a.sph[s];
+  gnb = dnb = d.nbs;
+  if (a.kind == kPassZ) {
     f0 = (t - d.ztile) * a.fc;
-    nf = d.ncol * d.nb;
+    nf = d.ncol * d.nel;
     tab += d.gidx_off;
     gat = d.sph_off;
     den = d.col_off;
     pstride = d.colrow;
+    gnb = d.nb;
+    tail_g = V == 2 && (d.nb & 1);
   } else {
     const int ft = t % a.tiles, rest = t / a.tiles;
     const int pl = a.kind == kPassX ? rest / a.rtiles : rest;  // plane within the group
-    const int p = a.p0 + pl;
-    s = p / a.nz;
-    const int z = p - s * a.nz;
-    const PassSph d = a.sph[s];
+    const int z = a.p0 + pl - s * a.nz;
     f0 = ft * a.fc;
     if (a.kind == kPassY) {
-      nf = d.nslab * d.nb;
+      nf = d.nslab * d.nel;
       tab += d.colidx_off;
       gat = d.col_off + static_cast<int64_t>(z) * d.colrow;
       den = static_cast<int64_t>(pl) * a.splane;
@@ -113,7 +183,7 @@ __global__ void __launch_bounds__(pass_max_threads(N, sizeof(T) == 8)) pass_kern
     } else {
       const int y0 = (rest - pl * a.rtiles) * a.lines;
       nl = min(a.lines, a.ny - y0);
-      nf = d.nb;
+      nf = d.nel;
       trow = 0;
       tab += d.xinv_off;
       gat = static_cast<int64_t>(pl) * a.splane + static_cast<int64_t>(y0) * d.srow;
@@ -122,140 +192,322 @@ __global__ void __launch_bounds__(pass_max_threads(N, sizeof(T) == 8)) pass_kern
       den = d.grid_off + vrow * d.nb;
       dstep = N * d.nb;
       pstride = d.nb;
+      dnb = d.nb;
+      tail_d = V == 2 && (d.nb & 1);
     }
     if (f0 >= nf) return;
   }
-  const int nb = a.sph[s].nb;
+  const int nel = d.nel;
   const int fc = a.fc, nfl = min(fc, nf - f0);
-  const float inv_fc = 1.0f / static_cast<float>(fc), inv_nb = 1.0f / static_cast<float>(nb);
-  const int c0 = f0 / nb, b0 = f0 - c0 * nb;  // line and band of element f0
-  const cpx<T>* gsrc = src + gat;             // inverse: gathered, forward: dense
-  const cpx<T>* dsrc = src + den + f0;
-  cpx<T>* gdst = dst + gat;
-  cpx<T>* ddst = dst + den + f0;
+  const float inv_fc = 1.0f / static_cast<float>(fc), inv_nel = 1.0f / static_cast<float>(nel);
+  const int c0 = f0 / nel, e0 = f0 - c0 * nel;  // line and element of the line at f0
   const bool ntd = a.nt_dense != 0, ntg = a.nt_gather != 0;
+
+  // the tile's table rows in LDS as byte offsets (a.tab_lds: the host has
+  // checked that the gathered region and the dense side span less than 2 GiB)
+  if constexpr (R2 > 1) {
+    if (a.tab_lds) {
+      const int nlin = (e0 + nfl - 1) / nel + 1;
+      const int32_t* __restrict__ row = tab + static_cast<int64_t>(c0) * trow;
+      const unsigned step = static_cast<unsigned>(gnb) * es;
+      for (int i = threadIdx.x; i < nlin * N; i += blockDim.x) {
+        const int g = row[i];
+        ltab[i] = g >= 0 ? static_cast<unsigned>(g) * step : kPassAbsent;
+      }
+    }
+  }
 
   // stage 1: thread (f, i, l) takes positions i + R2*q of line l
   const int items1 = a.lines * R2 * fc;
-  cpx<T> v[R1];
-  auto load = [&](int it) {
+  cpx<T> va[R1], vb[V == 2 ? R1 : 1];  // the lane's bands
+#define FFTB_SET(q, e)                  \
+  do {                                  \
+    const Elem<T, V> e_ = (e);          \
+    va[q].re = e_.a.re;                 \
+    va[q].im = e_.a.im;                 \
+    if constexpr (V == 2) {             \
+      vb[q].re = e_.b.re;               \
+      vb[q].im = e_.b.im;               \
+    }                                   \
+  } while (0)
+  auto load = [&](int it) __attribute__((always_inline)) {
     const int rest = pass_div(it, fc, inv_fc);
     const int f = it - rest * fc, l = rest / R2, i = rest - l * R2;
     const bool ok = f < nfl && l < nl;
+    const int ee = e0 + (ok ? f : 0);
+    const int dc = pass_div(ee, nel, inv_nel);
+    const int band = V * (ee - dc * nel);
+#pragma unroll
+    for (int q = 0; q < R1; ++q) FFTB_SET(q, (Elem<T, V>{{0, 0}, {0, 0}}));
+    if (!ok) return;
     if constexpr (S > 0) {
-      const int bb = b0 + (ok ? f : 0);
-      const int dc = pass_div(bb, nb, inv_nb);
+      const bool half = tail_g && ee - dc * nel == nel - 1;
+      const cpx<T>* gsrc = src + gat;
+      if (R2 > 1 && a.tab_lds) {
+        const __amdgpu_buffer_rsrc_t r = pass_rsrc(gsrc);
+        const unsigned off = static_cast<unsigned>(band + l * gstep) * es;
+        const unsigned* row = ltab + (trow ? dc * N : 0) + i;
+        if (!half) {
+          with_nt(ntg, [&](auto nt) __attribute__((always_inline)) {
+#pragma unroll
+            for (int q = 0; q < R1; ++q)
+              FFTB_SET(q, (buf_ld_el<decltype(nt)::value, V, T>(r, row[R2 * q] + off, 0)));
+          });
+        } else {
+#pragma unroll
+          for (int q = 0; q < R1; ++q) va[q] = buf_ld_el<false, 1, T>(r, row[R2 * q] + off, 0).a;
+        }
+        return;
+      }
       const int32_t* __restrict__ row = tab + static_cast<int64_t>(c0 + dc) * trow + i;
-      const cpx<T>* base = gsrc + (bb - dc * nb) + l * gstep;
+      const cpx<T>* base = gsrc + band + l * gstep;
       int g[R1];
 #pragma unroll
-      for (int q = 0; q < R1; ++q) g[q] = ok ? row[R2 * q] : -1;
-      with_nt(ntg, [&](auto nt) {
+      for (int q = 0; q < R1; ++q) g[q] = row[R2 * q];
+      if (!half) {
+        with_nt(ntg, [&](auto nt) __attribute__((always_inline)) {
+#pragma unroll
+          for (int q = 0; q < R1; ++q)
+            if (g[q] >= 0)
+              FFTB_SET(q, (ld_el<decltype(nt)::value, V>(base + static_cast<int64_t>(g[q]) * gnb)));
+        });
+      } else {
 #pragma unroll
         for (int q = 0; q < R1; ++q)
-          v[q] = g[q] >= 0 ? ld_c<decltype(nt)::value>(base + static_cast<int64_t>(g[q]) * nb)
-                           : cpx<T>{0, 0};
-      });
+          if (g[q] >= 0) va[q] = ld_el<false, 1>(base + static_cast<int64_t>(g[q]) * gnb).a;
+      }
     } else {
-      const cpx<T>* base = dsrc + f + i * pstride + static_cast<int64_t>(l) * dstep;
-      with_nt(ntd, [&](auto nt) {
+      const bool half = tail_d && ee - dc * nel == nel - 1;
+      const cpx<T>* dsrc = src + den + static_cast<int64_t>(c0) * dnb;
+      const int64_t lane = dc * dnb + band + i * pstride + static_cast<int64_t>(l) * dstep;
+      if (!half) {
+        if (a.tab_lds) {
+          const __amdgpu_buffer_rsrc_t r = pass_rsrc(dsrc);
+          const unsigned off = static_cast<unsigned>(lane) * es;
+          const unsigned step = __builtin_amdgcn_readfirstlane(static_cast<unsigned>(R2 * pstride) * es);
+          with_nt(ntd, [&](auto nt) __attribute__((always_inline)) {
 #pragma unroll
-        for (int q = 0; q < R1; ++q)
-          v[q] = ok ? ld_c<decltype(nt)::value>(base + (R2 * q) * pstride) : cpx<T>{0, 0};
-      });
+            for (int q = 0; q < R1; ++q)
+              FFTB_SET(q, (buf_ld_el<decltype(nt)::value, V, T>(r, off, q * step)));
+          });
+        } else {
+          with_nt(ntd, [&](auto nt) __attribute__((always_inline)) {
+#pragma unroll
+            for (int q = 0; q < R1; ++q)
+              FFTB_SET(q, (ld_el<decltype(nt)::value, V>(dsrc + lane + (R2 * q) * pstride)));
+          });
+        }
+      } else {
+#pragma unroll
+        for (int q = 0; q < R1; ++q) va[q] = ld_el<false, 1>(dsrc + lane + (R2 * q) * pstride).a;
+      }
     }
   };
   // stage 2 (or the only stage): thread (f, k1, l) writes positions k1 + R1*k2
-  auto emit = [&](int f, int l, int k1, auto& u, auto stride_c, auto count_c) {
+  auto emit = [&](int f, int l, int k1, auto& ua, auto& ub, auto stride_c, auto count_c)
+      __attribute__((always_inline)) {
     constexpr int ST = decltype(stride_c)::value, CT = decltype(count_c)::value;
     if (f >= nfl || l >= nl) return;
+    const int ee = e0 + f;
+    const int dc = pass_div(ee, nel, inv_nel);
+    const int band = V * (ee - dc * nel);
+#define FFTB_GET(k) ua[k].re, ua[k].im, ub[V == 2 ? (k) : 0].re, ub[V == 2 ? (k) : 0].im
     if constexpr (S > 0) {
-      if (a.pot) {
-        const T* __restrict__ vr = reinterpret_cast<const T*>(a.pot) + vrow + static_cast<int64_t>(l) * N + k1;
-#pragma unroll
-        for (int k = 0; k < CT; ++k) u[k] = cscale(u[k], vr[ST * k]);
+      const T* __restrict__ vr = reinterpret_cast<const T*>(a.pot) + vrow + static_cast<int64_t>(l) * N + k1;
+      if constexpr (V == 2) {
+        // (a factor of 1 where there is no potential: a branch around the
+        // products took 20-35 more registers; complex128 is the other way round)
+        T pot[CT];
+        static_for<0, CT>([&](auto kc) __attribute__((always_inline)) { pot[decltype(kc)::value] = 1; });
+        if (a.pot)
+          static_for<0, CT>([&](auto kc) __attribute__((always_inline)) {
+            pot[decltype(kc)::value] = vr[ST * decltype(kc)::value];
+          });
+        static_for<0, CT>([&](auto kc) __attribute__((always_inline)) {
+          constexpr int k = decltype(kc)::value;
+          ua[k].re *= pot[k];
+          ua[k].im *= pot[k];
+          ub[k].re *= pot[k];
+          ub[k].im *= pot[k];
+        });
+      } else if (a.pot) {
+        static_for<0, CT>([&](auto kc) __attribute__((always_inline)) {
+          constexpr int k = decltype(kc)::value;
+          ua[k] = cscale(ua[k], vr[ST * k]);
+        });
       }
-      cpx<T>* base = ddst + f + k1 * pstride + static_cast<int64_t>(l) * dstep;
-      with_nt(ntd, [&](auto nt) {
-#pragma unroll
-        for (int k = 0; k < CT; ++k) st_c<decltype(nt)::value>(base + (ST * k) * pstride, u[k]);
-      });
+      const bool half = tail_d && ee - dc * nel == nel - 1;
+      cpx<T>* ddst = dst + den + static_cast<int64_t>(c0) * dnb;
+      const int64_t lane = dc * dnb + band + k1 * pstride + static_cast<int64_t>(l) * dstep;
+      if (!half) {
+        if (R2 > 1 && a.tab_lds) {
+          const __amdgpu_buffer_rsrc_t r = pass_rsrc(ddst);
+          const unsigned off = static_cast<unsigned>(lane) * es;
+          const unsigned step = __builtin_amdgcn_readfirstlane(static_cast<unsigned>(ST * pstride) * es);
+          with_nt(ntd, [&](auto nt) __attribute__((always_inline)) {
+            static_for<0, CT>([&](auto kc) __attribute__((always_inline)) {
+              constexpr int k = decltype(kc)::value;
+              buf_st_el<decltype(nt)::value, V>(r, FFTB_GET(k), off, k * step);
+            });
+          });
+        } else {
+          with_nt(ntd, [&](auto nt) __attribute__((always_inline)) {
+            static_for<0, CT>([&](auto kc) __attribute__((always_inline)) {
+              constexpr int k = decltype(kc)::value;
+              st_el<decltype(nt)::value, V>(ddst + lane + (ST * k) * pstride, FFTB_GET(k));
+            });
+          });
+        }
+      } else {
+        static_for<0, CT>([&](auto kc) __attribute__((always_inline)) {
+          constexpr int k = decltype(kc)::value;
+          st_el<false, 1>(ddst + lane + (ST * k) * pstride, ua[k].re, ua[k].im, T(0), T(0));
+        });
+      }
     } else {
-      const int bb = b0 + f;
-      const int dc = pass_div(bb, nb, inv_nb);
-      const int32_t* __restrict__ row = tab + static_cast<int64_t>(c0 + dc) * trow + k1;
-      cpx<T>* base = gdst + (bb - dc * nb) + l * gstep;
+      const bool half = tail_g && ee - dc * nel == nel - 1;
       const T sc = static_cast<T>(a.scale);
-      int g[CT];
-#pragma unroll
-      for (int k = 0; k < CT; ++k) g[k] = row[ST * k];
-      with_nt(ntg, [&](auto nt) {
-#pragma unroll
-        for (int k = 0; k < CT; ++k)
-          if (g[k] >= 0) st_c<decltype(nt)::value>(base + static_cast<int64_t>(g[k]) * nb, cscale(u[k], sc));
+      static_for<0, CT>([&](auto kc) __attribute__((always_inline)) {
+        constexpr int k = decltype(kc)::value;
+        ua[k].re *= sc;
+          ua[k].im *= sc;
+        if constexpr (V == 2) {
+            ub[k].re *= sc;
+            ub[k].im *= sc;
+          }
       });
+      cpx<T>* gdst = dst + gat;
+      if (R2 > 1 && a.tab_lds) {
+        const __amdgpu_buffer_rsrc_t r = pass_rsrc(gdst);
+        const unsigned off = static_cast<unsigned>(band + l * gstep) * es;
+        const unsigned* row = ltab + (trow ? dc * N : 0) + k1;
+        if (!half) {
+          with_nt(ntg, [&](auto nt) __attribute__((always_inline)) {
+            static_for<0, CT>([&](auto kc) __attribute__((always_inline)) {
+              constexpr int k = decltype(kc)::value;
+              buf_st_el<decltype(nt)::value, V>(r, FFTB_GET(k), row[ST * k] + off, 0);
+            });
+          });
+        } else {
+          static_for<0, CT>([&](auto kc) __attribute__((always_inline)) {
+            constexpr int k = decltype(kc)::value;
+            buf_st_el<false, 1>(r, ua[k].re, ua[k].im, T(0), T(0), row[ST * k] + off, 0);
+          });
+        }
+        return;
+      }
+      const int32_t* __restrict__ row = tab + static_cast<int64_t>(c0 + dc) * trow + k1;
+      cpx<T>* base = gdst + band + l * gstep;
+      int g[CT];
+      static_for<0, CT>([&](auto kc) __attribute__((always_inline)) {
+        constexpr int k = decltype(kc)::value;
+        g[k] = row[ST * k];
+      });
+      if (!half) {
+        with_nt(ntg, [&](auto nt) __attribute__((always_inline)) {
+          static_for<0, CT>([&](auto kc) __attribute__((always_inline)) {
+            constexpr int k = decltype(kc)::value;
+            if (g[k] >= 0)
+              st_el<decltype(nt)::value, V>(base + static_cast<int64_t>(g[k]) * gnb, FFTB_GET(k));
+          });
+        });
+      } else {
+        static_for<0, CT>([&](auto kc) __attribute__((always_inline)) {
+          constexpr int k = decltype(kc)::value;
+          if (g[k] >= 0) st_el<false, 1>(base + static_cast<int64_t>(g[k]) * gnb, ua[k].re, ua[k].im, T(0), T(0));
+        });
+      }
     }
   };
 
   if constexpr (R2 == 1) {
     for (int it = threadIdx.x; it < items1; it += blockDim.x) {
       load(it);
-      dft<R1, S>(v);
+      dft<R1, S>(va);
+      if constexpr (V == 2) dft<R1, S>(vb);
       const int l = pass_div(it, fc, inv_fc);
-      emit(it - l * fc, l, 0, v, std::integral_constant<int, 1>{}, std::integral_constant<int, R1>{});
+      emit(it - l * fc, l, 0, va, vb, std::integral_constant<int, 1>{}, std::integral_constant<int, R1>{});
     }
     return;
   } else {
     // (the host gives every item of either stage its own thread)
     const int it = threadIdx.x;
     const bool on1 = it < items1;
-    if (on1) load(it);
+    if (S < 0 && on1) load(it);
     bl_fill_twiddles<S, T>(tw, reinterpret_cast<const cpx<T>*>(a.root),
                            reinterpret_cast<const cpx<T>*>(a.root_lo), R1, R2);
     __syncthreads();
+    if (S > 0 && on1) load(it);
     const int rest1 = pass_div(it, fc, inv_fc);
     const int f = it - rest1 * fc;
     const int l1 = rest1 / R2, i1 = rest1 - l1 * R2;
     const int l2 = rest1 / R1, k1 = rest1 - l2 * R1;
     const bool on2 = it < a.lines * R1 * fc;
     if (on1) {
-      dft<R1, S>(v);
       const TwEntry<T>* tr = tw + i1 * tw_row_stride(R1);
-#pragma unroll
-      for (int k = 1; k < R1; ++k) {
-        const TwEntry<T> w = tr[k];
-        if constexpr (std::is_same<T, float>::value)
-          v[k] = cmul_hl(v[k], cpx<float>{w.re, w.im}, cpx<float>{w.lre, w.lim});
-        else
-          v[k] = cmul(v[k], cpx<double>{w.re, w.im});
+      auto twiddle = [](cpx<T> x, const TwEntry<T>& e) __attribute__((always_inline)) {
+        if constexpr (std::is_same<T, float>::value) return cmul_hl(x, {e.re, e.im}, {e.lre, e.lim});
+        else return cmul(x, {e.re, e.im});
+      };
+      dft<R1, S>(va);
+      if constexpr (V == 2) {
+        __builtin_amdgcn_sched_barrier(0);  // (one transform's temporaries at a time)
+        dft<R1, S>(vb);
+        __builtin_amdgcn_sched_barrier(0);
       }
+      static_for<1, R1>([&](auto kc) __attribute__((always_inline)) {
+        constexpr int k = decltype(kc)::value;
+        const TwEntry<T> e = tr[k];
+        va[k] = twiddle(va[k], e);
+        if constexpr (V == 2) vb[k] = twiddle(vb[k], e);
+      });
     }
-    T* out = buf + (l1 * R1 * RS + i1) * fc + f;
-    const T* in = buf + (l2 * R1 + k1) * RS * fc + f;
-    cpx<T> u[R2];
+    Part* out = buf + (l1 * R1 * RS + i1) * fc + f;
+    const Part* in = buf + (l2 * R1 + k1) * RS * fc + f;
+    cpx<T> ua[R2], ub[V == 2 ? R2 : 1];
     if (on1) {
-#pragma unroll
-      for (int k = 0; k < R1; ++k) out[k * RS * fc] = v[k].re;
+      static_for<0, R1>([&](auto kc) __attribute__((always_inline)) {
+        constexpr int k = decltype(kc)::value;
+        if constexpr (V == 2) out[k * RS * fc] = Part{va[k].re, vb[k].re};
+        else out[k * RS * fc] = Part{va[k].re};
+      });
     }
     __syncthreads();
     if (on2) {
-#pragma unroll
-      for (int i = 0; i < R2; ++i) u[i].re = in[i * fc];
+      static_for<0, R2>([&](auto ic) __attribute__((always_inline)) {
+        constexpr int i = decltype(ic)::value;
+        const Part x = in[i * fc];
+        ua[i].re = x[0];
+        if constexpr (V == 2) ub[i].re = x[1];
+      });
     }
     __syncthreads();
     if (on1) {
-#pragma unroll
-      for (int k = 0; k < R1; ++k) out[k * RS * fc] = v[k].im;
+      static_for<0, R1>([&](auto kc) __attribute__((always_inline)) {
+        constexpr int k = decltype(kc)::value;
+        if constexpr (V == 2) out[k * RS * fc] = Part{va[k].im, vb[k].im};
+        else out[k * RS * fc] = Part{va[k].im};
+      });
     }
     __syncthreads();
     if (on2) {
-#pragma unroll
-      for (int i = 0; i < R2; ++i) u[i].im = in[i * fc];
-      dft<R2, S>(u);
-      emit(f, l2, k1, u, std::integral_constant<int, R1>{}, std::integral_constant<int, R2>{});
+      static_for<0, R2>([&](auto ic) __attribute__((always_inline)) {
+        constexpr int i = decltype(ic)::value;
+        const Part x = in[i * fc];
+        ua[i].im = x[0];
+        if constexpr (V == 2) ub[i].im = x[1];
+      });
+      dft<R2, S>(ua);
+      if constexpr (V == 2) {
+        __builtin_amdgcn_sched_barrier(0);
+        dft<R2, S>(ub);
+      }
+      emit(f, l2, k1, ua, ub, std::integral_constant<int, R1>{}, std::integral_constant<int, R2>{});
     }
   }
 }
+#undef FFTB_SET
+#undef FFTB_GET
 
 // Lengths compiled, by translation-unit part.
 #define FFTB_PASS_LENGTHS_0(X) \
@@ -269,23 +521,23 @@ __global__ void __launch_bounds__(pass_max_threads(N, sizeof(T) == 8)) pass_kern
   X(270) X(288) X(300) X(320) X(324) X(360) X(375) X(384) X(400) X(405) X(432) X(450) X(480) \
   X(486) X(500) X(512)
 
-template <int S, typename T, int N>
+template <int S, typename T, int V, int N>
 hipError_t pass_one(const PassArgs& a, int threads, size_t lds, hipStream_t st, bool attr_only) {
   if (attr_only)
-    return hipFuncSetAttribute(reinterpret_cast<const void*>(pass_kernel<S, T, N>),
+    return hipFuncSetAttribute(reinterpret_cast<const void*>(pass_kernel<S, T, V, N>),
                                hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(lds));
-  hipLaunchKernelGGL((pass_kernel<S, T, N>), dim3(pass_grid(a.total, a.group)), dim3(threads), lds, st, a);
+  hipLaunchKernelGGL((pass_kernel<S, T, V, N>), dim3(pass_grid(a.total, a.group)), dim3(threads), lds, st, a);
   return hipGetLastError();
 }
 
 // Launch (or, with attr_only, allow `lds` bytes to) the kernel of length n if
 // part P compiles it; *found tells.
-template <int S, typename T, int P>
+template <int S, typename T, int V, int P>
 hipError_t pass_part(int n, const PassArgs& a, int threads, size_t lds, hipStream_t st,
                      bool attr_only, bool* found) {
   *found = true;
 #define FFTB_X(n_) \
-  case n_: return pass_one<S, T, n_>(a, threads, lds, st, attr_only);
+  case n_: return pass_one<S, T, V, n_>(a, threads, lds, st, attr_only);
   if constexpr (P == 0) {
     switch (n) { FFTB_PASS_LENGTHS_0(FFTB_X) }
   } else if constexpr (P == 1) {
@@ -300,8 +552,8 @@ hipError_t pass_part(int n, const PassArgs& a, int threads, size_t lds, hipStrea
   return hipErrorInvalidValue;
 }
 
-#define FFTB_PASS_INST(EXT, S, T, P)                                                             \
-  EXT template hipError_t pass_part<S, T, P>(int, const PassArgs&, int, size_t, hipStream_t, bool, \
+#define FFTB_PASS_INST(EXT, S, T, V, P)                                                          \
+  EXT template hipError_t pass_part<S, T, V, P>(int, const PassArgs&, int, size_t, hipStream_t, bool, \
                                              bool*);
 
 }  // namespace fftb

@@ -30,10 +30,10 @@ constexpr int pass_r1(int n) {
   return 0;
 }
 
-// Threads per workgroup the kernels are compiled for (FP64 lines of longer
+// Threads per workgroup the kernels are compiled for (16-byte elements of longer
 // codelets need more than the 128 registers that 1024 threads leave).
-constexpr int pass_max_threads(int n, bool fp64) {
-  return !fp64 || pass_r1(n) <= 12 ? 1024 : 512;
+constexpr int pass_max_threads(int n, bool small) {
+  return small || pass_r1(n) <= 12 ? 1024 : 512;
 }
 // Blocks of a launch whose tiles go to the XCDs in runs of `group`.
 constexpr int pass_grid(int total, int group) {
@@ -41,14 +41,18 @@ constexpr int pass_grid(int total, int group) {
 }
 
 enum { kPassZ = 0, kPassY = 1, kPassX = 2 };
+// What a lane holds of a point: one complex64, two neighbouring bands of
+// complex64, one complex128 value.
+enum PassElem { kElemC64 = 0, kElemC64x2 = 1, kElemC128 = 2 };
 
-// Per-sphere descriptor (device resident); offsets in complex elements (data)
-// or int32 entries (tables).
+// Per-sphere descriptor (device resident); offsets and strides in complex
+// values (data) or int32 entries (tables).
 struct PassSph {
   int64_t sph_off, grid_off, col_off;
-  int64_t colrow;      // element stride between z planes of the column scratch
+  int64_t colrow;      // stride between z planes of the column scratch
   int32_t nb, ncol, nslab;
-  int32_t srow;        // element stride between y rows of a slab plane
+  int32_t nel, nbs;    // elements per band vector, and its stride in the scratch
+  int32_t srow;        // stride between y rows of a slab plane
   int32_t gidx_off;    // ncol*nz: (column slot, z) -> coefficient or -1
   int32_t colidx_off;  // nslab*ny: (slab, y) -> column slot or -1
   int32_t xinv_off;    // nx: x -> slab or -1
@@ -65,8 +69,10 @@ struct PassArgs {
   int group;           // consecutive tiles that run on one XCD
   int fc, lines;       // a tile: fc elements of the fast dimension x `lines` rows (x)
   int lds_tw;          // byte offset of the twiddle table in LDS
+  int lds_tab;         // byte offset of the staged table rows
+  int tab_lds;         // stage the tile's table rows in LDS, 32-bit offsets on both sides
   int nt_dense, nt_gather;  // streaming accesses on either side
-  int64_t splane;      // element stride between planes of the slab scratch
+  int64_t splane;      // stride between planes of the slab scratch
   const PassSph* sph;
   const int32_t* tab;  // gidx / colidx / xinv
   const void *root, *root_lo;  // exp(-2*pi*i*j/n) (FP32: hi and lo)
@@ -82,7 +88,8 @@ struct PassTile {
   int tiles = 0, rtiles = 0;
   int group = 1;  // consecutive tiles that share an XCD
   size_t lds = 0;
-  int lds_tw = 0;
+  int lds_tw = 0, lds_tab = 0;
+  bool tab_lds = false;
 };
 
 struct PassPlan {
@@ -90,16 +97,17 @@ struct PassPlan {
   std::vector<int32_t> gidx, colidx, xinv;
   PassTile tz, ty, tx;
   int ztotal = 0;         // tiles of the z pass
+  PassElem elem = kElemC64;
   int nplanes = 0;        // planes of all spheres
   int group = 0;          // planes per y/x launch pair
-  int64_t splane = 0;     // slab scratch elements per plane
-  int64_t col_elems = 0;  // column scratch elements
+  int64_t splane = 0;     // slab scratch values per plane
+  int64_t col_elems = 0;  // column scratch values
   int64_t s_elems() const { return splane * group; }
 };
 
 // Build the pass plan; false where a length has no split or a size does not
-// fit its index types. colrow_max: per sphere the most elements a z plane of
-// its columns may take (the padded row is used only within it); s_budget: the
+// fit its index types. colrow_max: per sphere the most values a z plane of
+// its columns may take (rows are padded only within it); s_budget: the
 // most bytes the slab scratch of one group should take.
 bool build_pass_plan(int nx, int ny, int nz, bool fp64, const std::vector<SphereTables>& sph,
                      const std::vector<int64_t>& colrow_max, int64_t s_budget, PassPlan& out);

@@ -1,6 +1,6 @@
-// Axis-pass kernels: float forward, lengths of part 0.
+// Axis-pass kernels: complex64, forward, lengths of part 0.
 #include "kernels_pass.hpp"
 
 namespace fftb {
-FFTB_PASS_INST(, -1, float, 0)
+FFTB_PASS_INST(, -1, float, 1, 0)
 }  // namespace fftb

@@ -1,6 +1,6 @@
-// Axis-pass kernels: float forward, lengths of part 3.
+// Axis-pass kernels: complex64, forward, lengths of part 3.
 #include "kernels_pass.hpp"
 
 namespace fftb {
-FFTB_PASS_INST(, -1, float, 3)
+FFTB_PASS_INST(, -1, float, 1, 3)
 }  // namespace fftb

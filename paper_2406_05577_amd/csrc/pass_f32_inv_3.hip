@@ -1,6 +1,6 @@
-// Axis-pass kernels: float inverse, lengths of part 3.
+// Axis-pass kernels: complex64, inverse, lengths of part 3.
 #include "kernels_pass.hpp"
 
 namespace fftb {
-FFTB_PASS_INST(, +1, float, 3)
+FFTB_PASS_INST(, +1, float, 1, 3)
 }  // namespace fftb

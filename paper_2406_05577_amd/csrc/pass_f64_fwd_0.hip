@@ -1,6 +1,6 @@
-// Axis-pass kernels: double forward, lengths of part 0.
+// Axis-pass kernels: complex128, forward, lengths of part 0.
 #include "kernels_pass.hpp"
 
 namespace fftb {
-FFTB_PASS_INST(, -1, double, 0)
+FFTB_PASS_INST(, -1, double, 1, 0)
 }  // namespace fftb

@@ -1,6 +1,6 @@
-// Axis-pass kernels: double forward, lengths of part 2.
+// Axis-pass kernels: complex128, forward, lengths of part 2.
 #include "kernels_pass.hpp"
 
 namespace fftb {
-FFTB_PASS_INST(, -1, double, 2)
+FFTB_PASS_INST(, -1, double, 1, 2)
 }  // namespace fftb

@@ -1,6 +1,6 @@
-// Axis-pass kernels: double inverse, lengths of part 1.
+// Axis-pass kernels: complex128, inverse, lengths of part 1.
 #include "kernels_pass.hpp"
 
 namespace fftb {
-FFTB_PASS_INST(, +1, double, 1)
+FFTB_PASS_INST(, +1, double, 1, 1)
 }  // namespace fftb

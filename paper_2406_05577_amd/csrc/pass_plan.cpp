@@ -9,31 +9,36 @@ namespace fftb {
 namespace {
 
 constexpr size_t kPassLdsMax = 160 * 1024 - 1024;
+// LDS spent on staged table rows: a few lines' worth
+constexpr size_t kPassTabMax = 8 * 1024;
 
-// A tile of a pass over lines of length n: about 256 items per stage in whole
-// 128-byte pieces of the fast dimension (nf elements, the sphere's bands or
-// its flattened (line, band) index), and for short fast dimensions several
-// rows.
-bool make_tile(int n, bool fp64, int64_t nf, int nrows, bool even, PassTile& t) {
-  const int es = fp64 ? 16 : 8, w = 128 / es;
+// A tile of a pass over lines of length n: at most 256 items per stage (four
+// waves: a fifth, mostly idle one cost the 144-point inverse passes 10-35 %,
+// and 200 points over 320 threads 10-20 %) in whole 128-byte pieces of the fast
+// dimension (nf elements of `es` bytes, the sphere's bands or its flattened
+// (line, band) index), and for short fast dimensions several rows. even: the
+// fast dimension is cut into equal shares. ragged: the band vectors are no
+// whole 128-byte lines; a tile then takes them whole where it can.
+bool make_tile(int n, int es, int64_t nf, int nrows, bool even, bool ragged, PassTile& t) {
+  const int w = 128 / es;
   const int r1 = pass_r1(n);
   if (!r1) return false;
-  const int r2 = n / r1, m = std::max(r1, r2) == n ? 1 : std::max(r1, r2);
-  int target = std::max(1, (256 / m + w / 2) / w) * w;
+  const int r2 = n / r1, m = r2 == 1 ? 1 : std::max(r1, r2);
+  int target = std::max(1, 256 / (m * w)) * w;
   const auto lds_of = [&](int fc, int lines) {
     return r2 > 1 ? static_cast<size_t>(lines) * fc * r1 * (r2 | 1) * (es / 2) : size_t{0};
   };
   const size_t tab = r2 > 1 ? static_cast<size_t>(r1 | 1) * r2 * 16 : 0;
   while (target > w && lds_of(target, 1) + tab > kPassLdsMax / 2) target -= w;
-  const int most = pass_max_threads(n, fp64);
+  const int most = pass_max_threads(n, es == 8);
   if (2 * nf <= 3 * static_cast<int64_t>(target) ||
-      (even && nf % w != 0 && nf * m <= most && lds_of(static_cast<int>(nf), 1) + tab <= kPassLdsMax / 2)) {
+      (even && ragged && nf * m <= most && lds_of(static_cast<int>(nf), 1) + tab <= kPassLdsMax / 2)) {
     t.fc = static_cast<int>(nf);
   } else if (even) {
     // equal shares of the bands, in whole pieces where the bands are
     const int64_t nch = std::max<int64_t>(1, (nf + target / 2) / target);
     int64_t fc = (nf + nch - 1) / nch;
-    if (nf % w == 0) fc = (fc + w - 1) / w * w;
+    if (!ragged) fc = (fc + w - 1) / w * w;
     t.fc = static_cast<int>(fc);
   } else {
     t.fc = target;
@@ -43,10 +48,20 @@ bool make_tile(int n, bool fp64, int64_t nf, int nrows, bool even, PassTile& t) 
   if (r2 == 1) t.threads = std::min(t.threads, 256);
   const size_t b = (lds_of(t.fc, t.lines) + 15) & ~size_t{15};
   t.lds_tw = static_cast<int>(b);
+  t.lds_tab = static_cast<int>(b + tab);
   t.lds = b + tab;
   t.tiles = static_cast<int>((nf + t.fc - 1) / t.fc);
   t.rtiles = (nrows + t.lines - 1) / t.lines;
   return t.lds <= kPassLdsMax && t.threads <= most;
+}
+
+// Stage the table rows of a tile (of at most `lines` lines) in LDS where they
+// are few and both sides span less than 2 GiB.
+void stage_tables(int n, int64_t lines, int64_t span, PassTile& t) {
+  const size_t b = static_cast<size_t>(lines) * n * 4;
+  if (n == pass_r1(n) || b > kPassTabMax || span >= (int64_t{1} << 31)) return;
+  t.tab_lds = true;
+  t.lds += b;
 }
 
 }  // namespace
@@ -56,16 +71,37 @@ bool build_pass_plan(int nx, int ny, int nz, bool fp64, const std::vector<Sphere
   P = PassPlan();
   if (nx > kPassMaxN || ny > kPassMaxN || nz > kPassMaxN) return false;
   if (!pass_r1(nx) || !pass_r1(ny) || !pass_r1(nz)) return false;
-  const int es = fp64 ? 16 : 8;
-  const int64_t w = 128 / es;
+  const int cs = fp64 ? 16 : 8;     // bytes per value
+  const int64_t cw = 128 / cs;      // values per 128-byte line
   const int64_t N = static_cast<int64_t>(nx) * ny * nz;
-  const auto pad = [w](int64_t v) { return (v + w - 1) / w * w; };
+  const auto pad = [cw](int64_t v) { return (v + cw - 1) / cw * cw; };
+  // complex64: two bands per lane, unless too many lanes would hold one (the
+  // last of an odd count)
+  int v = fp64 ? 1 : 2;
+  for (size_t i = 0; i < sph.size(); ++i) {
+    if (sph[i].nb >= (1 << 20)) return false;
+    if (v == 2 && sph[i].nb % 2 && (sph[i].nb < 7 || static_cast<int64_t>(sph[i].ncol) * (sph[i].nb + 1) > colrow_max[i]))
+      v = 1;
+  }
+  P.elem = fp64 ? kElemC128 : v == 2 ? kElemC64x2 : kElemC64;
+  const int es = cs * v;  // bytes per element
   int64_t soff = 0, goff = 0, coff = 0, max_col = 0, max_slab = 0;
-  int32_t max_nb = 0;
+  int64_t span_z = 0, span_y = 0, span_x = 0;  // bytes of the larger side of a tile's accesses
+  int32_t max_nel = 0, min_nel = 1 << 30;
+  bool ragged = false;
   for (size_t i = 0; i < sph.size(); ++i) {
     const SphereTables& s = sph[i];
-    if (s.nb >= (1 << 20) || static_cast<int64_t>(s.ncol) * s.nb >= (int64_t{1} << 30) ||
-        static_cast<int64_t>(s.nslab) * s.nb >= (int64_t{1} << 30))
+    PassSph d = {};
+    d.sph_off = soff;
+    d.grid_off = goff;
+    d.col_off = coff;
+    d.nb = s.nb;
+    d.nel = (s.nb + v - 1) / v;
+    d.nbs = d.nel * v;
+    d.ncol = s.ncol;
+    d.nslab = s.nslab;
+    if (static_cast<int64_t>(s.ncol) * d.nbs >= (int64_t{1} << 30) ||
+        static_cast<int64_t>(s.nslab) * d.nbs >= (int64_t{1} << 30))
       return false;
     // column slots by (y, x): the columns of a y row are neighbours, as the
     // slabs of a slab row are, so that the y pass reads and writes runs
@@ -74,16 +110,9 @@ bool build_pass_plan(int nx, int ny, int nz, bool fp64, const std::vector<Sphere
     std::sort(order.begin(), order.end(), [&s](int32_t a, int32_t b) {
       return s.col_y[a] != s.col_y[b] ? s.col_y[a] < s.col_y[b] : s.col_xi[a] < s.col_xi[b];
     });
-    PassSph d = {};
-    d.sph_off = soff;
-    d.grid_off = goff;
-    d.col_off = coff;
-    d.nb = s.nb;
-    d.ncol = s.ncol;
-    d.nslab = s.nslab;
-    const int64_t row = static_cast<int64_t>(s.ncol) * s.nb;
+    const int64_t row = static_cast<int64_t>(s.ncol) * d.nbs;
     d.colrow = pad(row) <= colrow_max[i] ? pad(row) : row;
-    d.srow = static_cast<int32_t>(pad(static_cast<int64_t>(s.nslab) * s.nb));
+    d.srow = static_cast<int32_t>(pad(static_cast<int64_t>(s.nslab) * d.nbs));
     if (P.gidx.size() + static_cast<size_t>(s.ncol) * nz >= (size_t{1} << 31)) return false;
     d.gidx_off = static_cast<int32_t>(P.gidx.size());
     d.colidx_off = static_cast<int32_t>(P.colidx.size());
@@ -100,23 +129,30 @@ bool build_pass_plan(int nx, int ny, int nz, bool fp64, const std::vector<Sphere
     soff += s.ns * s.nb;
     goff += N * s.nb;
     coff += d.colrow * nz;
-    max_col = std::max(max_col, row);
-    max_slab = std::max(max_slab, static_cast<int64_t>(s.nslab) * s.nb);
-    max_nb = std::max(max_nb, s.nb);
+    max_col = std::max(max_col, static_cast<int64_t>(s.ncol) * d.nel);
+    max_slab = std::max(max_slab, static_cast<int64_t>(s.nslab) * d.nel);
+    max_nel = std::max(max_nel, d.nel);
+    min_nel = std::min(min_nel, d.nel);
+    ragged = ragged || s.nb % cw != 0;
+    span_z = std::max(span_z, std::max(s.ns * s.nb, d.colrow * nz) * cs);
+    span_y = std::max(span_y, std::max(d.colrow, static_cast<int64_t>(d.srow) * ny) * cs);
+    span_x = std::max(span_x, static_cast<int64_t>(ny) * std::max<int64_t>(nx * static_cast<int64_t>(s.nb), d.srow) * cs);
     P.splane = std::max(P.splane, static_cast<int64_t>(d.srow) * ny);
     P.sph.push_back(d);
   }
   P.col_elems = coff;
   P.nplanes = static_cast<int>(sph.size()) * nz;
-  if (!make_tile(nz, fp64, max_col, 1, false, P.tz) || !make_tile(ny, fp64, max_slab, 1, false, P.ty) ||
-      !make_tile(nx, fp64, max_nb, ny, true, P.tx))
+  if (!make_tile(nz, es, max_col, 1, false, ragged, P.tz) ||
+      !make_tile(ny, es, max_slab, 1, false, ragged, P.ty) ||
+      !make_tile(nx, es, max_nel, ny, true, ragged, P.tx))
     return false;
+  stage_tables(nz, (P.tz.fc - 1 + min_nel - 1) / min_nel + 1, span_z, P.tz);
+  stage_tables(ny, (P.ty.fc - 1 + min_nel - 1) / min_nel + 1, span_y, P.ty);
+  stage_tables(nx, 1, span_x, P.tx);
   // tiles that cut the band vectors of a ragged band count inside a 128-byte
   // line meet their neighbours in one L2 (whole lines spread over the XCDs:
   // sending 16 runs of whole lines to one XCD took 10.0 ms instead of 7.9 ms at
   // 128^3, 256 complex128 bands)
-  bool ragged = false;
-  for (const auto& d : P.sph) ragged = ragged || d.nb % w != 0;
   if (ragged) {
     P.tz.group = 4;
     P.ty.group = P.ty.tiles;
@@ -124,10 +160,10 @@ bool build_pass_plan(int nx, int ny, int nz, bool fp64, const std::vector<Sphere
   }
   for (auto& d : P.sph) {
     d.ztile = P.ztotal;
-    P.ztotal += static_cast<int>((static_cast<int64_t>(d.ncol) * d.nb + P.tz.fc - 1) / P.tz.fc);
+    P.ztotal += static_cast<int>((static_cast<int64_t>(d.ncol) * d.nel + P.tz.fc - 1) / P.tz.fc);
   }
   // equal groups of planes within the budget
-  const int64_t most = std::max<int64_t>(1, s_budget / (P.splane * es));
+  const int64_t most = std::max<int64_t>(1, s_budget / (P.splane * cs));
   const int64_t groups = (P.nplanes + most - 1) / most;
   P.group = static_cast<int>((P.nplanes + groups - 1) / groups);
   return static_cast<int64_t>(P.group) * std::max(P.ty.tiles, P.tx.tiles * P.tx.rtiles) < (int64_t{1} << 31);

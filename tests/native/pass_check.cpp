@@ -38,23 +38,28 @@ static void walk(const PassPlan& P, int kind, int nx, int ny, int nz, int p0, in
   const int n = kind == kPassZ ? nz : kind == kPassY ? ny : nx;
   const int r1 = pass_r1(n), r2 = n / r1;
   const int total = kind == kPassZ ? P.ztotal : kind == kPassY ? np * t.tiles : np * t.tiles * t.rtiles;
+  const int v = P.elem == kElemC64x2 ? 2 : 1;
   const std::vector<int32_t>& table = kind == kPassZ ? P.gidx : kind == kPassY ? P.colidx : P.xinv;
   CHECK(t.threads >= 64 && t.threads % 64 == 0);
   CHECK(t.lds_tw + (r2 > 1 ? (r1 | 1) * r2 * 16 : 0) <= static_cast<int>(t.lds));
   for (int b = 0; b < total; ++b) {
     size_t s = 0;
     int f0, nf, nl = 1, trow = n, tab;
-    int64_t gat, den, pstride, gstep = 0, dstep = 0;
+    int64_t gat, den, pstride, gstep = 0, dstep = 0, gnb, dnb;
+    bool tail_g = false, tail_d = false;
     if (kind == kPassZ) {
       while (s + 1 < P.sph.size() && b >= P.sph[s + 1].ztile) ++s;
       const PassSph& d = P.sph[s];
       f0 = (b - d.ztile) * t.fc;
-      nf = d.ncol * d.nb;
+      nf = d.ncol * d.nel;
       CHECK(f0 < nf);
       tab = d.gidx_off;
       gat = d.sph_off;
       den = d.col_off;
       pstride = d.colrow;
+      gnb = d.nb;
+      dnb = d.nbs;
+      tail_g = v == 2 && d.nb % 2;
     } else {
       const int ft = b % t.tiles, rest = b / t.tiles;
       const int pl = kind == kPassX ? rest / t.rtiles : rest;
@@ -64,15 +69,16 @@ static void walk(const PassPlan& P, int kind, int nx, int ny, int nz, int p0, in
       const PassSph& d = P.sph[s];
       f0 = ft * t.fc;
       if (kind == kPassY) {
-        nf = d.nslab * d.nb;
+        nf = d.nslab * d.nel;
         tab = d.colidx_off;
         gat = d.col_off + z * d.colrow;
         den = pl * P.splane;
         pstride = d.srow;
+        gnb = dnb = d.nbs;
       } else {
         const int y0 = (rest - pl * t.rtiles) * t.lines;
         nl = std::min(t.lines, ny - y0);
-        nf = d.nb;
+        nf = d.nel;
         trow = 0;
         tab = d.xinv_off;
         gat = pl * P.splane + static_cast<int64_t>(y0) * d.srow;
@@ -80,20 +86,38 @@ static void walk(const PassPlan& P, int kind, int nx, int ny, int nz, int p0, in
         den = d.grid_off + (static_cast<int64_t>(z) * ny + y0) * n * d.nb;
         dstep = static_cast<int64_t>(n) * d.nb;
         pstride = d.nb;
+        gnb = d.nbs;
+        dnb = d.nb;
+        tail_d = v == 2 && d.nb % 2;
       }
       if (f0 >= nf) continue;
     }
-    const int nb = P.sph[s].nb, nfl = std::min(t.fc, nf - f0), c0 = f0 / nb, b0 = f0 - c0 * nb;
+    const int nel = P.sph[s].nel, nfl = std::min(t.fc, nf - f0), c0 = f0 / nel, e0 = f0 - c0 * nel;
+    const int nlin = (e0 + nfl - 1) / nel + 1;
+    // the staged table rows: nlin lines (x: one row of the table for all)
+    if (t.tab_lds) {
+      CHECK(static_cast<size_t>(t.lds_tab) + static_cast<size_t>(nlin) * n * 4 <= t.lds);
+      CHECK(tab + static_cast<int64_t>(c0) * trow + static_cast<int64_t>(nlin) * n <= static_cast<int64_t>(table.size()));
+      if (kind == kPassX) CHECK(nlin == 1);
+    }
     for (int l = 0; l < t.lines; ++l)
       for (int f = 0; f < t.fc; ++f) {
         if (f >= nfl || l >= nl) continue;
-        const int bb = b0 + f, dc = bb / nb;
+        const int ee = e0 + f, dc = ee / nel, j = ee - dc * nel, band = v * j;
+        CHECK(dc < nlin);
         for (int pos = 0; pos < n; ++pos) {
           const int64_t ti = tab + static_cast<int64_t>(c0 + dc) * trow + pos;
           CHECK(ti >= 0 && ti < static_cast<int64_t>(table.size()));
           const int g = table[ti];
-          if (g >= 0) gather.at(gat + static_cast<int64_t>(g) * nb + (bb - dc * nb) + l * gstep);
-          dense.at(den + f0 + f + pos * pstride + l * dstep);
+          for (int w = 0; w < v; ++w) {
+            const bool last = w == 1 && j == nel - 1;
+            const int64_t go = g * gnb + band + w + l * gstep;
+            const int64_t d_o = static_cast<int64_t>(c0) * dnb + dc * dnb + band + w + pos * pstride + l * dstep;
+            if (t.tab_lds && g >= 0) CHECK(go * 8 * (P.elem == kElemC128 ? 2 : 1) < (int64_t{1} << 31));
+            if (t.tab_lds) CHECK((d_o - c0 * dnb) * 8 * (P.elem == kElemC128 ? 2 : 1) < (int64_t{1} << 31));
+            if (g >= 0 && !(tail_g && last)) gather.at(gat + go);
+            if (!(tail_d && last)) dense.at(den + d_o);
+          }
         }
       }
   }
@@ -125,7 +149,7 @@ static void check(std::mt19937& g, int nx, int ny, int nz, bool fp64, const std:
     std::string err;
     CHECK(build_sphere_tables(nx, ny, nz, m.data(), static_cast<int64_t>(m.size()), nb, t, err) == 0);
     sph.push_back(t);
-    row_max.push_back(static_cast<int64_t>(t.ncol) * nb + (g() % 2 ? 64 : 0));
+    row_max.push_back(static_cast<int64_t>(t.ncol) * (nb + (nb % 2 && g() % 2)) + (g() % 2 ? 64 : 0));
     sphere += t.ns * nb;
     grid += static_cast<int64_t>(nx) * ny * nz * nb;
   }
@@ -135,10 +159,10 @@ static void check(std::mt19937& g, int nx, int ny, int nz, bool fp64, const std:
   CHECK(P.nplanes == nz * static_cast<int>(nbs.size()) && P.group >= 1);
   int64_t cols = 0, slabs = 0, colrows = 0;
   for (size_t i = 0; i < sph.size(); ++i) {
-    cols += static_cast<int64_t>(sph[i].ncol) * sph[i].nb * nz;
+    cols += static_cast<int64_t>(sph[i].ncol) * P.sph[i].nbs * nz;
     CHECK(P.sph[i].colrow <= row_max[i]);
     colrows += P.sph[i].colrow * nz;
-    slabs += static_cast<int64_t>(sph[i].nslab) * sph[i].nb * ny * nz;
+    slabs += static_cast<int64_t>(sph[i].nslab) * P.sph[i].nbs * ny * nz;
   }
   CHECK(colrows == P.col_elems);
   Touch tsph(sphere), tcol(P.col_elems);
