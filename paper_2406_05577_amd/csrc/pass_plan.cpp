@@ -2,7 +2,6 @@
 #include "pass.hpp"
 
 #include <algorithm>
-#include <numeric>
 
 namespace fftb {
 
@@ -85,6 +84,10 @@ bool build_pass_plan(int nx, int ny, int nz, bool fp64, const std::vector<Sphere
   }
   P.elem = fp64 ? kElemC128 : v == 2 ? kElemC64x2 : kElemC64;
   const int es = cs * v;  // bytes per element
+  size_t entries = 0;
+  for (const auto& s : sph) entries += static_cast<size_t>(s.ncol) * nz;
+  if (entries >= (size_t{1} << 31)) return false;
+  P.gidx.reserve(entries);
   int64_t soff = 0, goff = 0, coff = 0, max_col = 0, max_slab = 0;
   int64_t span_z = 0, span_y = 0, span_x = 0;  // bytes of the larger side of a tile's accesses
   int32_t max_nel = 0, min_nel = 1 << 30;
@@ -105,20 +108,18 @@ bool build_pass_plan(int nx, int ny, int nz, bool fp64, const std::vector<Sphere
       return false;
     // column slots by (y, x): the columns of a y row are neighbours, as the
     // slabs of a slab row are, so that the y pass reads and writes runs
-    std::vector<int32_t> order(s.ncol);
-    std::iota(order.begin(), order.end(), 0);
-    std::sort(order.begin(), order.end(), [&s](int32_t a, int32_t b) {
-      return s.col_y[a] != s.col_y[b] ? s.col_y[a] < s.col_y[b] : s.col_xi[a] < s.col_xi[b];
-    });
+    // (the columns come ordered by (x, y): one bucket per y keeps the x order)
+    std::vector<int32_t> start(ny + 1, 0), order(s.ncol);
+    for (int32_t c = 0; c < s.ncol; ++c) ++start[s.col_y[c] + 1];
+    for (int y = 0; y < ny; ++y) start[y + 1] += start[y];
+    for (int32_t c = 0; c < s.ncol; ++c) order[start[s.col_y[c]]++] = c;
     const int64_t row = static_cast<int64_t>(s.ncol) * d.nbs;
     d.colrow = pad(row) <= colrow_max[i] ? pad(row) : row;
     d.srow = static_cast<int32_t>(pad(static_cast<int64_t>(s.nslab) * d.nbs));
-    if (P.gidx.size() + static_cast<size_t>(s.ncol) * nz >= (size_t{1} << 31)) return false;
     d.gidx_off = static_cast<int32_t>(P.gidx.size());
     d.colidx_off = static_cast<int32_t>(P.colidx.size());
     d.xinv_off = static_cast<int32_t>(P.xinv.size());
     P.colidx.resize(P.colidx.size() + static_cast<size_t>(s.nslab) * ny, -1);
-    P.gidx.reserve(P.gidx.size() + static_cast<size_t>(s.ncol) * nz);
     for (int32_t slot = 0; slot < s.ncol; ++slot) {
       const int32_t c = order[slot];
       P.colidx[d.colidx_off + static_cast<size_t>(s.col_xi[c]) * ny + s.col_y[c]] = slot;

@@ -109,8 +109,7 @@ int build_sphere_tables(int nx, int ny, int nz, const int32_t* map, int64_t ns, 
   if (ns > N) { err = "more coefficients than grid points"; return -1; }
   st.ns = ns;
   st.nb = nb;
-  // range and uniqueness
-  std::vector<int32_t> sorted(map, map + ns);
+  // range (uniqueness is checked where the entries are placed)
   for (int64_t g = 0; g < ns; ++g)
     if (map[g] < 0 || map[g] >= N) {
       char buf[128];
@@ -119,20 +118,12 @@ int build_sphere_tables(int nx, int ny, int nz, const int32_t* map, int64_t ns, 
       err = buf;
       return -1;
     }
-  std::sort(sorted.begin(), sorted.end());
-  for (int64_t g = 1; g < ns; ++g)
-    if (sorted[g] == sorted[g - 1]) {
-      char buf[96];
-      std::snprintf(buf, sizeof buf, "duplicate map entry %d", sorted[g]);
-      err = buf;
-      return -1;
-    }
   // columns: distinct (x, y), ordered by (x, y)
   std::vector<int32_t> colkey(static_cast<size_t>(nx) * ny, -1);
   std::vector<char> xocc(nx, 0);
   for (int64_t g = 0; g < ns; ++g) {
-    const int32_t v = map[g];
-    const int x = v % nx, y = (v / nx) % ny;
+    const int32_t row = map[g] / nx;
+    const int x = map[g] - row * nx, y = row % ny;
     colkey[static_cast<size_t>(x) * ny + y] = 0;
     xocc[x] = 1;
   }
@@ -168,10 +159,21 @@ int build_sphere_tables(int nx, int ny, int nz, const int32_t* map, int64_t ns, 
   st.entry_col.resize(ns);
   st.entry_z.resize(ns);
   for (int64_t g = 0; g < ns; ++g) {
-    const int32_t v = map[g];
-    const int x = v % nx, y = (v / nx) % ny, z = v / (nx * ny);
+    const int32_t row = map[g] / nx;
+    const int x = map[g] - row * nx, z = row / ny, y = row - z * ny;
     const int c = colkey[static_cast<size_t>(x) * ny + y];
-    st.gidx[static_cast<size_t>(c) * nz + z] = static_cast<int32_t>(g);
+    int32_t& entry = st.gidx[static_cast<size_t>(c) * nz + z];
+    if (entry >= 0) {
+      // report the smallest duplicate
+      std::vector<int32_t> sorted(map, map + ns);
+      std::sort(sorted.begin(), sorted.end());
+      char buf[96];
+      std::snprintf(buf, sizeof buf, "duplicate map entry %d",
+                    *std::adjacent_find(sorted.begin(), sorted.end()));
+      err = buf;
+      return -1;
+    }
+    entry = static_cast<int32_t>(g);
     st.entry_col[g] = c;
     st.entry_z[g] = z;
   }
