@@ -151,15 +151,13 @@ __global__ void __launch_bounds__(pass_max_threads(N, sizeof(T) * V == 4)) pass_
   const cpx<T>* src = reinterpret_cast<const cpx<T>*>(a.src);
   cpx<T>* dst = reinterpret_cast<cpx<T>*>(a.dst);
   int64_t gat, den, pstride, vrow = 0;
-  int gstep = 0, dstep = 0, gnb, dnb;  // row steps, band strides of the two sides
-  bool tail_g = false, tail_d = false;  // sides whose band vectors may end in half an element
+  int gstep = 0, dstep = 0;  // row steps
   if (a.kind == kPassZ) {
     while (s + 1 < a.nsph && t >= a.sph[s + 1].ztile) ++s;
   } else {
     s = (a.p0 + (a.kind == kPassX ? t / (a.tiles * a.rtiles) : t / a.tiles)) / a.nz;
   }
   const PassSph d = a.sph[s];
-  gnb = dnb = d.nbs;
   if (a.kind == kPassZ) {
     f0 = (t - d.ztile) * a.fc;
     nf = d.ncol * d.nel;
@@ -167,8 +165,6 @@ __global__ void __launch_bounds__(pass_max_threads(N, sizeof(T) * V == 4)) pass_
     gat = d.sph_off;
     den = d.col_off;
     pstride = d.colrow;
-    gnb = d.nb;
-    tail_g = V == 2 && (d.nb & 1);
   } else {
     const int ft = t % a.tiles, rest = t / a.tiles;
     const int pl = a.kind == kPassX ? rest / a.rtiles : rest;  // plane within the group
@@ -192,12 +188,10 @@ __global__ void __launch_bounds__(pass_max_threads(N, sizeof(T) * V == 4)) pass_
       den = d.grid_off + vrow * d.nb;
       dstep = N * d.nb;
       pstride = d.nb;
-      dnb = d.nb;
-      tail_d = V == 2 && (d.nb & 1);
     }
     if (f0 >= nf) return;
   }
-  const int nel = d.nel;
+  const int nel = d.nel, nb = d.nb;
   const int fc = a.fc, nfl = min(fc, nf - f0);
   const float inv_fc = 1.0f / static_cast<float>(fc), inv_nel = 1.0f / static_cast<float>(nel);
   const int c0 = f0 / nel, e0 = f0 - c0 * nel;  // line and element of the line at f0
@@ -209,7 +203,7 @@ __global__ void __launch_bounds__(pass_max_threads(N, sizeof(T) * V == 4)) pass_
     if (a.tab_lds) {
       const int nlin = (e0 + nfl - 1) / nel + 1;
       const int32_t* __restrict__ row = tab + static_cast<int64_t>(c0) * trow;
-      const unsigned step = static_cast<unsigned>(gnb) * es;
+      const unsigned step = static_cast<unsigned>(nb) * es;
       for (int i = threadIdx.x; i < nlin * N; i += blockDim.x) {
         const int g = row[i];
         ltab[i] = g >= 0 ? static_cast<unsigned>(g) * step : kPassAbsent;
@@ -241,22 +235,16 @@ __global__ void __launch_bounds__(pass_max_threads(N, sizeof(T) * V == 4)) pass_
     for (int q = 0; q < R1; ++q) FFTB_SET(q, (Elem<T, V>{{0, 0}, {0, 0}}));
     if (!ok) return;
     if constexpr (S > 0) {
-      const bool half = tail_g && ee - dc * nel == nel - 1;
       const cpx<T>* gsrc = src + gat;
       if (R2 > 1 && a.tab_lds) {
         const __amdgpu_buffer_rsrc_t r = pass_rsrc(gsrc);
         const unsigned off = static_cast<unsigned>(band + l * gstep) * es;
         const unsigned* row = ltab + (trow ? dc * N : 0) + i;
-        if (!half) {
-          with_nt(ntg, [&](auto nt) __attribute__((always_inline)) {
+        with_nt(ntg, [&](auto nt) __attribute__((always_inline)) {
 #pragma unroll
-            for (int q = 0; q < R1; ++q)
-              FFTB_SET(q, (buf_ld_el<decltype(nt)::value, V, T>(r, row[R2 * q] + off, 0)));
-          });
-        } else {
-#pragma unroll
-          for (int q = 0; q < R1; ++q) va[q] = buf_ld_el<false, 1, T>(r, row[R2 * q] + off, 0).a;
-        }
+          for (int q = 0; q < R1; ++q)
+            FFTB_SET(q, (buf_ld_el<decltype(nt)::value, V, T>(r, row[R2 * q] + off, 0)));
+        });
         return;
       }
       const int32_t* __restrict__ row = tab + static_cast<int64_t>(c0 + dc) * trow + i;
@@ -264,42 +252,29 @@ __global__ void __launch_bounds__(pass_max_threads(N, sizeof(T) * V == 4)) pass_
       int g[R1];
 #pragma unroll
       for (int q = 0; q < R1; ++q) g[q] = row[R2 * q];
-      if (!half) {
-        with_nt(ntg, [&](auto nt) __attribute__((always_inline)) {
-#pragma unroll
-          for (int q = 0; q < R1; ++q)
-            if (g[q] >= 0)
-              FFTB_SET(q, (ld_el<decltype(nt)::value, V>(base + static_cast<int64_t>(g[q]) * gnb)));
-        });
-      } else {
+      with_nt(ntg, [&](auto nt) __attribute__((always_inline)) {
 #pragma unroll
         for (int q = 0; q < R1; ++q)
-          if (g[q] >= 0) va[q] = ld_el<false, 1>(base + static_cast<int64_t>(g[q]) * gnb).a;
-      }
+          if (g[q] >= 0) FFTB_SET(q, (ld_el<decltype(nt)::value, V>(base + static_cast<int64_t>(g[q]) * nb)));
+      });
     } else {
-      const bool half = tail_d && ee - dc * nel == nel - 1;
-      const cpx<T>* dsrc = src + den + static_cast<int64_t>(c0) * dnb;
-      const int64_t lane = dc * dnb + band + i * pstride + static_cast<int64_t>(l) * dstep;
-      if (!half) {
-        if (a.tab_lds) {
-          const __amdgpu_buffer_rsrc_t r = pass_rsrc(dsrc);
-          const unsigned off = static_cast<unsigned>(lane) * es;
-          const unsigned step = __builtin_amdgcn_readfirstlane(static_cast<unsigned>(R2 * pstride) * es);
-          with_nt(ntd, [&](auto nt) __attribute__((always_inline)) {
+      const cpx<T>* dsrc = src + den + static_cast<int64_t>(c0) * nb;
+      const int64_t lane = dc * nb + band + i * pstride + static_cast<int64_t>(l) * dstep;
+      if (a.tab_lds) {
+        const __amdgpu_buffer_rsrc_t r = pass_rsrc(dsrc);
+        const unsigned off = static_cast<unsigned>(lane) * es;
+        const unsigned step = __builtin_amdgcn_readfirstlane(static_cast<unsigned>(R2 * pstride) * es);
+        with_nt(ntd, [&](auto nt) __attribute__((always_inline)) {
 #pragma unroll
-            for (int q = 0; q < R1; ++q)
-              FFTB_SET(q, (buf_ld_el<decltype(nt)::value, V, T>(r, off, q * step)));
-          });
-        } else {
-          with_nt(ntd, [&](auto nt) __attribute__((always_inline)) {
-#pragma unroll
-            for (int q = 0; q < R1; ++q)
-              FFTB_SET(q, (ld_el<decltype(nt)::value, V>(dsrc + lane + (R2 * q) * pstride)));
-          });
-        }
+          for (int q = 0; q < R1; ++q)
+            FFTB_SET(q, (buf_ld_el<decltype(nt)::value, V, T>(r, off, q * step)));
+        });
       } else {
+        with_nt(ntd, [&](auto nt) __attribute__((always_inline)) {
 #pragma unroll
-        for (int q = 0; q < R1; ++q) va[q] = ld_el<false, 1>(dsrc + lane + (R2 * q) * pstride).a;
+          for (int q = 0; q < R1; ++q)
+            FFTB_SET(q, (ld_el<decltype(nt)::value, V>(dsrc + lane + (R2 * q) * pstride)));
+        });
       }
     }
   };
@@ -336,36 +311,27 @@ __global__ void __launch_bounds__(pass_max_threads(N, sizeof(T) * V == 4)) pass_
           ua[k] = cscale(ua[k], vr[ST * k]);
         });
       }
-      const bool half = tail_d && ee - dc * nel == nel - 1;
-      cpx<T>* ddst = dst + den + static_cast<int64_t>(c0) * dnb;
-      const int64_t lane = dc * dnb + band + k1 * pstride + static_cast<int64_t>(l) * dstep;
-      if (!half) {
-        if (R2 > 1 && a.tab_lds) {
-          const __amdgpu_buffer_rsrc_t r = pass_rsrc(ddst);
-          const unsigned off = static_cast<unsigned>(lane) * es;
-          const unsigned step = __builtin_amdgcn_readfirstlane(static_cast<unsigned>(ST * pstride) * es);
-          with_nt(ntd, [&](auto nt) __attribute__((always_inline)) {
-            static_for<0, CT>([&](auto kc) __attribute__((always_inline)) {
-              constexpr int k = decltype(kc)::value;
-              buf_st_el<decltype(nt)::value, V>(r, FFTB_GET(k), off, k * step);
-            });
+      cpx<T>* ddst = dst + den + static_cast<int64_t>(c0) * nb;
+      const int64_t lane = dc * nb + band + k1 * pstride + static_cast<int64_t>(l) * dstep;
+      if (R2 > 1 && a.tab_lds) {
+        const __amdgpu_buffer_rsrc_t r = pass_rsrc(ddst);
+        const unsigned off = static_cast<unsigned>(lane) * es;
+        const unsigned step = __builtin_amdgcn_readfirstlane(static_cast<unsigned>(ST * pstride) * es);
+        with_nt(ntd, [&](auto nt) __attribute__((always_inline)) {
+          static_for<0, CT>([&](auto kc) __attribute__((always_inline)) {
+            constexpr int k = decltype(kc)::value;
+            buf_st_el<decltype(nt)::value, V>(r, FFTB_GET(k), off, k * step);
           });
-        } else {
-          with_nt(ntd, [&](auto nt) __attribute__((always_inline)) {
-            static_for<0, CT>([&](auto kc) __attribute__((always_inline)) {
-              constexpr int k = decltype(kc)::value;
-              st_el<decltype(nt)::value, V>(ddst + lane + (ST * k) * pstride, FFTB_GET(k));
-            });
-          });
-        }
+        });
       } else {
-        static_for<0, CT>([&](auto kc) __attribute__((always_inline)) {
-          constexpr int k = decltype(kc)::value;
-          st_el<false, 1>(ddst + lane + (ST * k) * pstride, ua[k].re, ua[k].im, T(0), T(0));
+        with_nt(ntd, [&](auto nt) __attribute__((always_inline)) {
+          static_for<0, CT>([&](auto kc) __attribute__((always_inline)) {
+            constexpr int k = decltype(kc)::value;
+            st_el<decltype(nt)::value, V>(ddst + lane + (ST * k) * pstride, FFTB_GET(k));
+          });
         });
       }
     } else {
-      const bool half = tail_g && ee - dc * nel == nel - 1;
       const T sc = static_cast<T>(a.scale);
       static_for<0, CT>([&](auto kc) __attribute__((always_inline)) {
         constexpr int k = decltype(kc)::value;
@@ -381,42 +347,27 @@ __global__ void __launch_bounds__(pass_max_threads(N, sizeof(T) * V == 4)) pass_
         const __amdgpu_buffer_rsrc_t r = pass_rsrc(gdst);
         const unsigned off = static_cast<unsigned>(band + l * gstep) * es;
         const unsigned* row = ltab + (trow ? dc * N : 0) + k1;
-        if (!half) {
-          with_nt(ntg, [&](auto nt) __attribute__((always_inline)) {
-            static_for<0, CT>([&](auto kc) __attribute__((always_inline)) {
-              constexpr int k = decltype(kc)::value;
-              buf_st_el<decltype(nt)::value, V>(r, FFTB_GET(k), row[ST * k] + off, 0);
-            });
-          });
-        } else {
+        with_nt(ntg, [&](auto nt) __attribute__((always_inline)) {
           static_for<0, CT>([&](auto kc) __attribute__((always_inline)) {
             constexpr int k = decltype(kc)::value;
-            buf_st_el<false, 1>(r, ua[k].re, ua[k].im, T(0), T(0), row[ST * k] + off, 0);
+            buf_st_el<decltype(nt)::value, V>(r, FFTB_GET(k), row[ST * k] + off, 0);
           });
-        }
+        });
         return;
       }
       const int32_t* __restrict__ row = tab + static_cast<int64_t>(c0 + dc) * trow + k1;
       cpx<T>* base = gdst + band + l * gstep;
       int g[CT];
       static_for<0, CT>([&](auto kc) __attribute__((always_inline)) {
-        constexpr int k = decltype(kc)::value;
-        g[k] = row[ST * k];
+        g[decltype(kc)::value] = row[ST * decltype(kc)::value];
       });
-      if (!half) {
-        with_nt(ntg, [&](auto nt) __attribute__((always_inline)) {
-          static_for<0, CT>([&](auto kc) __attribute__((always_inline)) {
-            constexpr int k = decltype(kc)::value;
-            if (g[k] >= 0)
-              st_el<decltype(nt)::value, V>(base + static_cast<int64_t>(g[k]) * gnb, FFTB_GET(k));
-          });
-        });
-      } else {
+      with_nt(ntg, [&](auto nt) __attribute__((always_inline)) {
         static_for<0, CT>([&](auto kc) __attribute__((always_inline)) {
           constexpr int k = decltype(kc)::value;
-          if (g[k] >= 0) st_el<false, 1>(base + static_cast<int64_t>(g[k]) * gnb, ua[k].re, ua[k].im, T(0), T(0));
+          if (g[k] >= 0)
+            st_el<decltype(nt)::value, V>(base + static_cast<int64_t>(g[k]) * nb, FFTB_GET(k));
         });
-      }
+      });
     }
   };
 

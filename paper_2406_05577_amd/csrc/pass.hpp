@@ -51,7 +51,7 @@ struct PassSph {
   int64_t sph_off, grid_off, col_off;
   int64_t colrow;      // stride between z planes of the column scratch
   int32_t nb, ncol, nslab;
-  int32_t nel, nbs;    // elements per band vector, and its stride in the scratch
+  int32_t nel;         // elements per band vector
   int32_t srow;        // stride between y rows of a slab plane
   int32_t gidx_off;    // ncol*nz: (column slot, z) -> coefficient or -1
   int32_t colidx_off;  // nslab*ny: (slab, y) -> column slot or -1

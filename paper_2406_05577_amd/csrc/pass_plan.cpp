@@ -30,12 +30,19 @@ bool make_tile(int n, int es, int64_t nf, int nrows, bool even, bool ragged, Pas
   const size_t tab = r2 > 1 ? static_cast<size_t>(r1 | 1) * r2 * 16 : 0;
   while (target > w && lds_of(target, 1) + tab > kPassLdsMax / 2) target -= w;
   const int most = pass_max_threads(n, es == 8);
-  if (2 * nf <= 3 * static_cast<int64_t>(target) ||
-      (even && ragged && nf * m <= most && lds_of(static_cast<int>(nf), 1) + tab <= kPassLdsMax / 2)) {
+  if (2 * nf <= 3 * static_cast<int64_t>(target)) {
     t.fc = static_cast<int>(nf);
   } else if (even) {
-    // equal shares of the bands, in whole pieces where the bands are
-    const int64_t nch = std::max<int64_t>(1, (nf + target / 2) / target);
+    // equal shares of the bands: in whole pieces where the bands are, else as
+    // few as eight waves and half the LDS allow (a cut leaves two half-written
+    // lines: 200x192x216, 20 complex128 bands, inverse x pass 1.60 ms in two
+    // tiles, 0.63 ms whole; more waves: 50x48x96, 82 bands, 0.39 against 0.32 ms)
+    int64_t share = target;
+    if (ragged) {
+      share = std::max(1, 512 / m);
+      while (share > target && lds_of(static_cast<int>(share), 1) + tab > kPassLdsMax / 2) --share;
+    }
+    const int64_t nch = ragged ? (nf + share - 1) / share : std::max<int64_t>(1, (nf + share / 2) / share);
     int64_t fc = (nf + nch - 1) / nch;
     if (!ragged) fc = (fc + w - 1) / w * w;
     t.fc = static_cast<int>(fc);
@@ -54,11 +61,13 @@ bool make_tile(int n, int es, int64_t nf, int nrows, bool even, bool ragged, Pas
   return t.lds <= kPassLdsMax && t.threads <= most;
 }
 
-// Stage the table rows of a tile (of at most `lines` lines) in LDS where they
-// are few and both sides span less than 2 GiB.
+// Stage the table rows of a tile (of at most `lines` lines) in LDS where a line's
+// row serves four lanes or more (with one band per line the staging only adds a
+// step: 81^3, 8 x 1 complex128 bands, y passes 29 -> 35 us) and both sides span
+// less than 2 GiB.
 void stage_tables(int n, int64_t lines, int64_t span, PassTile& t) {
   const size_t b = static_cast<size_t>(lines) * n * 4;
-  if (n == pass_r1(n) || b > kPassTabMax || span >= (int64_t{1} << 31)) return;
+  if (n == pass_r1(n) || b > kPassTabMax || 4 * lines > t.fc + 4 || span >= (int64_t{1} << 31)) return;
   t.tab_lds = true;
   t.lds += b;
 }
@@ -74,13 +83,13 @@ bool build_pass_plan(int nx, int ny, int nz, bool fp64, const std::vector<Sphere
   const int64_t cw = 128 / cs;      // values per 128-byte line
   const int64_t N = static_cast<int64_t>(nx) * ny * nz;
   const auto pad = [cw](int64_t v) { return (v + cw - 1) / cw * cw; };
-  // complex64: two bands per lane, unless too many lanes would hold one (the
-  // last of an odd count)
+  // complex64: two bands per lane where every count is even (odd counts would
+  // end their band vectors in half elements, whose separate stores took the
+  // inverse x pass of 240x200x250, 17 bands, from 0.77 to 2.9 ms)
   int v = fp64 ? 1 : 2;
-  for (size_t i = 0; i < sph.size(); ++i) {
-    if (sph[i].nb >= (1 << 20)) return false;
-    if (v == 2 && sph[i].nb % 2 && (sph[i].nb < 7 || static_cast<int64_t>(sph[i].ncol) * (sph[i].nb + 1) > colrow_max[i]))
-      v = 1;
+  for (const auto& s : sph) {
+    if (s.nb >= (1 << 20)) return false;
+    if (s.nb % 2) v = 1;
   }
   P.elem = fp64 ? kElemC128 : v == 2 ? kElemC64x2 : kElemC64;
   const int es = cs * v;  // bytes per element
@@ -99,12 +108,11 @@ bool build_pass_plan(int nx, int ny, int nz, bool fp64, const std::vector<Sphere
     d.grid_off = goff;
     d.col_off = coff;
     d.nb = s.nb;
-    d.nel = (s.nb + v - 1) / v;
-    d.nbs = d.nel * v;
+    d.nel = s.nb / v;
     d.ncol = s.ncol;
     d.nslab = s.nslab;
-    if (static_cast<int64_t>(s.ncol) * d.nbs >= (int64_t{1} << 30) ||
-        static_cast<int64_t>(s.nslab) * d.nbs >= (int64_t{1} << 30))
+    if (static_cast<int64_t>(s.ncol) * s.nb >= (int64_t{1} << 30) ||
+        static_cast<int64_t>(s.nslab) * s.nb >= (int64_t{1} << 30))
       return false;
     // column slots by (y, x): the columns of a y row are neighbours, as the
     // slabs of a slab row are, so that the y pass reads and writes runs
@@ -113,9 +121,9 @@ bool build_pass_plan(int nx, int ny, int nz, bool fp64, const std::vector<Sphere
     for (int32_t c = 0; c < s.ncol; ++c) ++start[s.col_y[c] + 1];
     for (int y = 0; y < ny; ++y) start[y + 1] += start[y];
     for (int32_t c = 0; c < s.ncol; ++c) order[start[s.col_y[c]]++] = c;
-    const int64_t row = static_cast<int64_t>(s.ncol) * d.nbs;
+    const int64_t row = static_cast<int64_t>(s.ncol) * s.nb;
     d.colrow = pad(row) <= colrow_max[i] ? pad(row) : row;
-    d.srow = static_cast<int32_t>(pad(static_cast<int64_t>(s.nslab) * d.nbs));
+    d.srow = static_cast<int32_t>(pad(static_cast<int64_t>(s.nslab) * s.nb));
     d.gidx_off = static_cast<int32_t>(P.gidx.size());
     d.colidx_off = static_cast<int32_t>(P.colidx.size());
     d.xinv_off = static_cast<int32_t>(P.xinv.size());
@@ -155,8 +163,8 @@ bool build_pass_plan(int nx, int ny, int nz, bool fp64, const std::vector<Sphere
   // sending 16 runs of whole lines to one XCD took 10.0 ms instead of 7.9 ms at
   // 128^3, 256 complex128 bands)
   if (ragged) {
-    P.tz.group = 4;
-    P.ty.group = P.ty.tiles;
+    P.tz.group = 8;
+    P.ty.group = std::min(8, P.ty.tiles);
     P.tx.group = P.tx.tiles;
   }
   for (auto& d : P.sph) {

@@ -45,8 +45,7 @@ static void walk(const PassPlan& P, int kind, int nx, int ny, int nz, int p0, in
   for (int b = 0; b < total; ++b) {
     size_t s = 0;
     int f0, nf, nl = 1, trow = n, tab;
-    int64_t gat, den, pstride, gstep = 0, dstep = 0, gnb, dnb;
-    bool tail_g = false, tail_d = false;
+    int64_t gat, den, pstride, gstep = 0, dstep = 0;
     if (kind == kPassZ) {
       while (s + 1 < P.sph.size() && b >= P.sph[s + 1].ztile) ++s;
       const PassSph& d = P.sph[s];
@@ -57,9 +56,6 @@ static void walk(const PassPlan& P, int kind, int nx, int ny, int nz, int p0, in
       gat = d.sph_off;
       den = d.col_off;
       pstride = d.colrow;
-      gnb = d.nb;
-      dnb = d.nbs;
-      tail_g = v == 2 && d.nb % 2;
     } else {
       const int ft = b % t.tiles, rest = b / t.tiles;
       const int pl = kind == kPassX ? rest / t.rtiles : rest;
@@ -74,7 +70,6 @@ static void walk(const PassPlan& P, int kind, int nx, int ny, int nz, int p0, in
         gat = d.col_off + z * d.colrow;
         den = pl * P.splane;
         pstride = d.srow;
-        gnb = dnb = d.nbs;
       } else {
         const int y0 = (rest - pl * t.rtiles) * t.lines;
         nl = std::min(t.lines, ny - y0);
@@ -86,13 +81,10 @@ static void walk(const PassPlan& P, int kind, int nx, int ny, int nz, int p0, in
         den = d.grid_off + (static_cast<int64_t>(z) * ny + y0) * n * d.nb;
         dstep = static_cast<int64_t>(n) * d.nb;
         pstride = d.nb;
-        gnb = d.nbs;
-        dnb = d.nb;
-        tail_d = v == 2 && d.nb % 2;
       }
       if (f0 >= nf) continue;
     }
-    const int nel = P.sph[s].nel, nfl = std::min(t.fc, nf - f0), c0 = f0 / nel, e0 = f0 - c0 * nel;
+    const int nb = P.sph[s].nb, nel = P.sph[s].nel, nfl = std::min(t.fc, nf - f0), c0 = f0 / nel, e0 = f0 - c0 * nel;
     const int nlin = (e0 + nfl - 1) / nel + 1;
     // the staged table rows: nlin lines (x: one row of the table for all)
     if (t.tab_lds) {
@@ -110,13 +102,12 @@ static void walk(const PassPlan& P, int kind, int nx, int ny, int nz, int p0, in
           CHECK(ti >= 0 && ti < static_cast<int64_t>(table.size()));
           const int g = table[ti];
           for (int w = 0; w < v; ++w) {
-            const bool last = w == 1 && j == nel - 1;
-            const int64_t go = g * gnb + band + w + l * gstep;
-            const int64_t d_o = static_cast<int64_t>(c0) * dnb + dc * dnb + band + w + pos * pstride + l * dstep;
+            const int64_t go = static_cast<int64_t>(g) * nb + band + w + l * gstep;
+            const int64_t d_o = static_cast<int64_t>(c0) * nb + dc * nb + band + w + pos * pstride + l * dstep;
             if (t.tab_lds && g >= 0) CHECK(go * 8 * (P.elem == kElemC128 ? 2 : 1) < (int64_t{1} << 31));
-            if (t.tab_lds) CHECK((d_o - c0 * dnb) * 8 * (P.elem == kElemC128 ? 2 : 1) < (int64_t{1} << 31));
-            if (g >= 0 && !(tail_g && last)) gather.at(gat + go);
-            if (!(tail_d && last)) dense.at(den + d_o);
+            if (t.tab_lds) CHECK((d_o - c0 * nb) * 8 * (P.elem == kElemC128 ? 2 : 1) < (int64_t{1} << 31));
+            if (g >= 0) gather.at(gat + go);
+            dense.at(den + d_o);
           }
         }
       }
@@ -149,7 +140,7 @@ static void check(std::mt19937& g, int nx, int ny, int nz, bool fp64, const std:
     std::string err;
     CHECK(build_sphere_tables(nx, ny, nz, m.data(), static_cast<int64_t>(m.size()), nb, t, err) == 0);
     sph.push_back(t);
-    row_max.push_back(static_cast<int64_t>(t.ncol) * (nb + (nb % 2 && g() % 2)) + (g() % 2 ? 64 : 0));
+    row_max.push_back(static_cast<int64_t>(t.ncol) * nb + (g() % 2 ? 64 : 0));
     sphere += t.ns * nb;
     grid += static_cast<int64_t>(nx) * ny * nz * nb;
   }
@@ -159,10 +150,10 @@ static void check(std::mt19937& g, int nx, int ny, int nz, bool fp64, const std:
   CHECK(P.nplanes == nz * static_cast<int>(nbs.size()) && P.group >= 1);
   int64_t cols = 0, slabs = 0, colrows = 0;
   for (size_t i = 0; i < sph.size(); ++i) {
-    cols += static_cast<int64_t>(sph[i].ncol) * P.sph[i].nbs * nz;
+    cols += static_cast<int64_t>(sph[i].ncol) * P.sph[i].nb * nz;
     CHECK(P.sph[i].colrow <= row_max[i]);
     colrows += P.sph[i].colrow * nz;
-    slabs += static_cast<int64_t>(sph[i].nslab) * P.sph[i].nbs * ny * nz;
+    slabs += static_cast<int64_t>(sph[i].nslab) * P.sph[i].nb * ny * nz;
   }
   CHECK(colrows == P.col_elems);
   Touch tsph(sphere), tcol(P.col_elems);
@@ -199,7 +190,8 @@ int main() {
   for (int it = 0; it < 60; ++it) {
     const int nx = len[g() % 17], ny = len[g() % 17], nz = len[g() % 17];
     std::vector<int> nbs;
-    for (unsigned i = 0; i < 1 + g() % 3; ++i) nbs.push_back(1 + static_cast<int>(g() % (it % 4 ? 9 : 70)));
+    const int even = it % 3 == 0 ? 2 : 1;  // two bands per lane, complex64
+    for (unsigned i = 0; i < 1 + g() % 3; ++i) nbs.push_back(even * (1 + static_cast<int>(g() % (it % 4 ? 9 : 70))));
     check(g, nx, ny, nz, it % 2, nbs, it % 5 ? 1.0 : 0.4, it % 7 ? 0.27 : 9.0, 1 << (10 + g() % 14));
   }
   check(g, 60, 4, 6, true, {37}, 1.0, 0.25, 1 << 20);
