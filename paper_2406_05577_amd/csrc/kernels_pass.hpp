@@ -103,12 +103,15 @@ __device__ __forceinline__ Elem<T, V> buf_ld_el(__amdgpu_buffer_rsrc_t r, unsign
   else
     return unpack<V, T>(__builtin_bit_cast(E, __builtin_amdgcn_raw_buffer_load_b64(r, off, soff, NT ? 2 : 0)));
 }
+// (No scalar offset here: the compiler takes a 16-byte store with one to have read
+// its data a cycle earlier and lets the next instruction overwrite them, which on
+// gfx950 changed the first word of a few lanes in one of 15 inverse transforms of
+// 60x54x50, 16 complex64 bands. Without one it waits.)
 template <bool NT, int V, typename T>
-__device__ __forceinline__ void buf_st_el(__amdgpu_buffer_rsrc_t r, T ar, T ai, T br, T bi, unsigned off,
-                                          unsigned soff) {
+__device__ __forceinline__ void buf_st_el(__amdgpu_buffer_rsrc_t r, T ar, T ai, T br, T bi, unsigned off) {
   const typename ElemVec<T, V>::words x = pack<V>(ar, ai, br, bi);
-  if constexpr (sizeof(x) == 16) __builtin_amdgcn_raw_buffer_store_b128(x, r, off, soff, NT ? 2 : 0);
-  else __builtin_amdgcn_raw_buffer_store_b64(x, r, off, soff, NT ? 2 : 0);
+  if constexpr (sizeof(x) == 16) __builtin_amdgcn_raw_buffer_store_b128(x, r, off, 0, NT ? 2 : 0);
+  else __builtin_amdgcn_raw_buffer_store_b64(x, r, off, 0, NT ? 2 : 0);
 }
 // Run f with the uniform flag nt as a constant. The fences keep the compiler
 // from merging the two copies, which would drop the non-temporal hint.
@@ -320,7 +323,7 @@ __global__ void __launch_bounds__(pass_max_threads(N, sizeof(T) * V == 4)) pass_
         with_nt(ntd, [&](auto nt) __attribute__((always_inline)) {
           static_for<0, CT>([&](auto kc) __attribute__((always_inline)) {
             constexpr int k = decltype(kc)::value;
-            buf_st_el<decltype(nt)::value, V>(r, FFTB_GET(k), off, k * step);
+            buf_st_el<decltype(nt)::value, V>(r, FFTB_GET(k), off + k * step);
           });
         });
       } else {
@@ -350,7 +353,7 @@ __global__ void __launch_bounds__(pass_max_threads(N, sizeof(T) * V == 4)) pass_
         with_nt(ntg, [&](auto nt) __attribute__((always_inline)) {
           static_for<0, CT>([&](auto kc) __attribute__((always_inline)) {
             constexpr int k = decltype(kc)::value;
-            buf_st_el<decltype(nt)::value, V>(r, FFTB_GET(k), row[ST * k] + off, 0);
+            buf_st_el<decltype(nt)::value, V>(r, FFTB_GET(k), row[ST * k] + off);
           });
         });
         return;

@@ -118,3 +118,26 @@ def test_pass_buffers_at_any_value(dtype, nb):
     for t in (s_all, g_all, b_all):
         assert t[0].item() == mark and t[-1].item() == mark
     p.close()
+
+
+@pytest.mark.parametrize("dtype", ["c128", "c64"])
+def test_pass_repeats(dtype):
+    """Every execution gives the same bits (a hazard between a store and the
+    next use of its registers showed in one of 15 executions)."""
+    import torch
+    w = _workload((60, 54, 50), 1, 16, dtype, 309)
+    sph = torch.from_numpy(w.sphere_concat()).to("cuda").to(
+        torch.complex128 if dtype == "c128" else torch.complex64)
+    p = make_plan(w, dtype=dtype)
+    pot = torch.rand(60 * 54 * 50, dtype=sph.real.dtype, device="cuda")
+
+    def results():
+        g = p.sphere_to_grid(sph)
+        vg = torch.empty_like(g)
+        return g, p.grid_to_sphere(g), p.apply_potential(sph, pot, vg), vg
+
+    first = results()
+    for _ in range(200):
+        assert all(torch.equal(torch.view_as_real(a), torch.view_as_real(b))
+                   for a, b in zip(results(), first))
+    p.close()
