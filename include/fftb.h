@@ -202,7 +202,8 @@ fftb_status fftb_grid_to_sphere(fftb_plan plan, const void* grid_in, void* spher
  * Kohn-Sham wavefunctions, and operations that are cheaper in real space):
  * for every band, psi = sphere_to_grid(c); psi(x,y,z) *= V(x,y,z);
  * c' = grid_to_sphere(psi). The multiply is fused into the stores of the
- * inverse plane kernel, so the step moves the bytes of one round trip.
+ * inverse plane kernel; axis passes (the default) also transform each x row back
+ * there, so that the grid is written but not read.
  * potential:  device pointer, N real values (double for FFTB_C128, float for
  *             FFTB_C64) in V[z][y][x] order, shared by all bands and spheres.
  * grid_work:  device pointer, info.grid_elems complex values; receives V*psi.
@@ -252,7 +253,8 @@ fftb_status fftb_plan_sphere_columns(fftb_plan plan, int32_t sphere, int32_t* co
  * 2: plane kernel, forward; 3: column kernel, forward; 4: class combine,
  * forward (plans whose forward plane kernel writes class partials). A direction
  * that runs as axis passes counts its z pass as the column kernel and its y and
- * x passes together as one launch of the plane kernel. */
+ * x passes together as one launch of the plane kernel; the potential step as axis
+ * passes counts all of its planes, both ways, at index 1. */
 typedef struct {
   int64_t launches[5];
   double total_ms[5];

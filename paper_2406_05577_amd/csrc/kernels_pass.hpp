@@ -20,6 +20,15 @@
 // LDS as byte offsets where they are few: one coalesced load in the place of R1
 // loads per thread, and buffer accesses that need no branch for absent entries.
 //
+// The potential step's x pass (POT) multiplies the inverse's rows by V on their
+// way to the grid and transforms them back in the same workgroup, into the slab
+// row that they came from: the grid is written but not read again.
+// 144x160x180, 128 complex128 bands: 2.6 ms, where the forward's x pass alone takes
+// 2.2 (the whole step 7.26 -> 5.42); its writes, grid and slab, go at 4.8 TB/s,
+// about what a pass that only writes the grid reaches. Arrays of their own after the second exchange keep it at 90
+// registers: with va and vb taken again, live wherever a lane has no item, it held
+// 132, a wave less per SIMD, and took 3.8 ms.
+//
 // Bound by memory: a pass reads and writes each value once (2.4 flop per byte
 // moved at 200 points), with enough workgroups in flight: the exchange sends the
 // real and the imaginary parts one after the other, half the LDS for two more
@@ -128,6 +137,18 @@ __device__ __forceinline__ void with_nt(bool nt, F&& f) {
   }
 }
 
+// the real or imaginary parts of an element (opaque as in pack)
+template <int V, typename T>
+__device__ __forceinline__ auto parts(T a, T b) {
+  typedef T P __attribute__((ext_vector_type(V)));
+  if constexpr (V == 1) {
+    return P{a};
+  } else {
+    asm("" : "+v"(a));
+    return P{a, b};
+  }
+}
+
 // floor(n / d) for 0 <= n < 2^22 through a float reciprocal and one correction
 __device__ __forceinline__ int pass_div(int n, int d, float inv_d) {
   int q = static_cast<int>(static_cast<float>(n) * inv_d);
@@ -136,7 +157,7 @@ __device__ __forceinline__ int pass_div(int n, int d, float inv_d) {
   return q;
 }
 
-template <int S, typename T, int V, int N>
+template <int S, typename T, int V, int N, bool POT>
 __global__ void __launch_bounds__(pass_max_threads(N, sizeof(T) * V == 4)) pass_kernel(const PassArgs a) {
   constexpr int R1 = pass_r1(N), R2 = N / R1, RS = R2 | 1;
   constexpr unsigned es = sizeof(cpx<T>);
@@ -281,106 +302,109 @@ __global__ void __launch_bounds__(pass_max_threads(N, sizeof(T) * V == 4)) pass_
       }
     }
   };
-  // stage 2 (or the only stage): thread (f, k1, l) writes positions k1 + R1*k2
-  auto emit = [&](int f, int l, int k1, auto& ua, auto& ub, auto stride_c, auto count_c)
+#define FFTB_GET(k) ua[k].re, ua[k].im, ub[V == 2 ? (k) : 0].re, ub[V == 2 ? (k) : 0].im
+  // the last stage of an inverse: thread (f, k1, l) writes positions k1 + ST*k
+  auto emit_dense = [&](int f, int l, int k1, auto& ua, auto& ub, auto stride_c, auto count_c)
       __attribute__((always_inline)) {
     constexpr int ST = decltype(stride_c)::value, CT = decltype(count_c)::value;
-    if (f >= nfl || l >= nl) return;
-    const int ee = e0 + f;
-    const int dc = pass_div(ee, nel, inv_nel);
-    const int band = V * (ee - dc * nel);
-#define FFTB_GET(k) ua[k].re, ua[k].im, ub[V == 2 ? (k) : 0].re, ub[V == 2 ? (k) : 0].im
-    if constexpr (S > 0) {
-      const T* __restrict__ vr = reinterpret_cast<const T*>(a.pot) + vrow + static_cast<int64_t>(l) * N + k1;
-      if constexpr (V == 2) {
-        // (a factor of 1 where there is no potential: a branch around the
-        // products took 20-35 more registers; complex128 is the other way round)
-        T pot[CT];
-        static_for<0, CT>([&](auto kc) __attribute__((always_inline)) { pot[decltype(kc)::value] = 1; });
-        if (a.pot)
-          static_for<0, CT>([&](auto kc) __attribute__((always_inline)) {
-            pot[decltype(kc)::value] = vr[ST * decltype(kc)::value];
-          });
+    const int dc = pass_div(e0 + f, nel, inv_nel);
+    const int band = V * (e0 + f - dc * nel);
+    cpx<T>* ddst = dst + den + static_cast<int64_t>(c0) * nb;
+    const int64_t lane = dc * nb + band + k1 * pstride + static_cast<int64_t>(l) * dstep;
+    if (R2 > 1 && a.tab_lds) {
+      const __amdgpu_buffer_rsrc_t r = pass_rsrc(ddst);
+      const unsigned off = static_cast<unsigned>(lane) * es;
+      const unsigned step = __builtin_amdgcn_readfirstlane(static_cast<unsigned>(ST * pstride) * es);
+      with_nt(ntd, [&](auto nt) __attribute__((always_inline)) {
         static_for<0, CT>([&](auto kc) __attribute__((always_inline)) {
           constexpr int k = decltype(kc)::value;
-          ua[k].re *= pot[k];
-          ua[k].im *= pot[k];
-          ub[k].re *= pot[k];
-          ub[k].im *= pot[k];
+          buf_st_el<decltype(nt)::value, V>(r, FFTB_GET(k), off + k * step);
         });
-      } else if (a.pot) {
-        static_for<0, CT>([&](auto kc) __attribute__((always_inline)) {
-          constexpr int k = decltype(kc)::value;
-          ua[k] = cscale(ua[k], vr[ST * k]);
-        });
-      }
-      cpx<T>* ddst = dst + den + static_cast<int64_t>(c0) * nb;
-      const int64_t lane = dc * nb + band + k1 * pstride + static_cast<int64_t>(l) * dstep;
-      if (R2 > 1 && a.tab_lds) {
-        const __amdgpu_buffer_rsrc_t r = pass_rsrc(ddst);
-        const unsigned off = static_cast<unsigned>(lane) * es;
-        const unsigned step = __builtin_amdgcn_readfirstlane(static_cast<unsigned>(ST * pstride) * es);
-        with_nt(ntd, [&](auto nt) __attribute__((always_inline)) {
-          static_for<0, CT>([&](auto kc) __attribute__((always_inline)) {
-            constexpr int k = decltype(kc)::value;
-            buf_st_el<decltype(nt)::value, V>(r, FFTB_GET(k), off + k * step);
-          });
-        });
-      } else {
-        with_nt(ntd, [&](auto nt) __attribute__((always_inline)) {
-          static_for<0, CT>([&](auto kc) __attribute__((always_inline)) {
-            constexpr int k = decltype(kc)::value;
-            st_el<decltype(nt)::value, V>(ddst + lane + (ST * k) * pstride, FFTB_GET(k));
-          });
-        });
-      }
+      });
     } else {
-      const T sc = static_cast<T>(a.scale);
-      static_for<0, CT>([&](auto kc) __attribute__((always_inline)) {
-        constexpr int k = decltype(kc)::value;
-        ua[k].re *= sc;
-          ua[k].im *= sc;
-        if constexpr (V == 2) {
-            ub[k].re *= sc;
-            ub[k].im *= sc;
-          }
-      });
-      cpx<T>* gdst = dst + gat;
-      if (R2 > 1 && a.tab_lds) {
-        const __amdgpu_buffer_rsrc_t r = pass_rsrc(gdst);
-        const unsigned off = static_cast<unsigned>(band + l * gstep) * es;
-        const unsigned* row = ltab + (trow ? dc * N : 0) + k1;
-        with_nt(ntg, [&](auto nt) __attribute__((always_inline)) {
-          static_for<0, CT>([&](auto kc) __attribute__((always_inline)) {
-            constexpr int k = decltype(kc)::value;
-            buf_st_el<decltype(nt)::value, V>(r, FFTB_GET(k), row[ST * k] + off);
-          });
-        });
-        return;
-      }
-      const int32_t* __restrict__ row = tab + static_cast<int64_t>(c0 + dc) * trow + k1;
-      cpx<T>* base = gdst + band + l * gstep;
-      int g[CT];
-      static_for<0, CT>([&](auto kc) __attribute__((always_inline)) {
-        g[decltype(kc)::value] = row[ST * decltype(kc)::value];
-      });
-      with_nt(ntg, [&](auto nt) __attribute__((always_inline)) {
+      with_nt(ntd, [&](auto nt) __attribute__((always_inline)) {
         static_for<0, CT>([&](auto kc) __attribute__((always_inline)) {
           constexpr int k = decltype(kc)::value;
-          if (g[k] >= 0)
-            st_el<decltype(nt)::value, V>(base + static_cast<int64_t>(g[k]) * nb, FFTB_GET(k));
+          st_el<decltype(nt)::value, V>(ddst + lane + (ST * k) * pstride, FFTB_GET(k));
         });
       });
     }
   };
+  // the last stage of a forward: the positions that the table keeps, to out
+  auto emit_gather = [&](cpx<T>* out, int f, int l, int k1, auto& ua, auto& ub, auto stride_c, auto count_c)
+      __attribute__((always_inline)) {
+    constexpr int ST = decltype(stride_c)::value, CT = decltype(count_c)::value;
+    const int dc = pass_div(e0 + f, nel, inv_nel);
+    const int band = V * (e0 + f - dc * nel);
+    cpx<T>* gdst = out + gat;
+    if (R2 > 1 && a.tab_lds) {
+      const __amdgpu_buffer_rsrc_t r = pass_rsrc(gdst);
+      const unsigned off = static_cast<unsigned>(band + l * gstep) * es;
+      const unsigned* row = ltab + (trow ? dc * N : 0) + k1;
+      with_nt(ntg, [&](auto nt) __attribute__((always_inline)) {
+        static_for<0, CT>([&](auto kc) __attribute__((always_inline)) {
+          constexpr int k = decltype(kc)::value;
+          buf_st_el<decltype(nt)::value, V>(r, FFTB_GET(k), row[ST * k] + off);
+        });
+      });
+      return;
+    }
+    const int32_t* __restrict__ row = tab + static_cast<int64_t>(c0 + dc) * trow + k1;
+    cpx<T>* base = gdst + band + l * gstep;
+    int g[CT];
+    static_for<0, CT>([&](auto kc) __attribute__((always_inline)) {
+      g[decltype(kc)::value] = row[ST * decltype(kc)::value];
+    });
+    with_nt(ntg, [&](auto nt) __attribute__((always_inline)) {
+      static_for<0, CT>([&](auto kc) __attribute__((always_inline)) {
+        constexpr int k = decltype(kc)::value;
+        if (g[k] >= 0)
+          st_el<decltype(nt)::value, V>(base + static_cast<int64_t>(g[k]) * nb, FFTB_GET(k));
+      });
+    });
+  };
+  // multiply by w (conjugated in the transform back)
+  auto twiddle = [](cpx<T> x, const TwEntry<T>& e, T sg) __attribute__((always_inline)) {
+    if constexpr (std::is_same<T, float>::value) return cmul_hl(x, {e.re, sg * e.im}, {e.lre, sg * e.lim});
+    else return cmul(x, {e.re, sg * e.im});
+  };
+  // scale by the potential at positions k1 + ST*k of line l, or by 1/N
+  auto weigh = [&](int l, int k1, auto& ua, auto& ub, auto stride_c, auto count_c)
+      __attribute__((always_inline)) {
+    constexpr int ST = decltype(stride_c)::value, CT = decltype(count_c)::value;
+    const T* __restrict__ vr = reinterpret_cast<const T*>(a.pot) + vrow + static_cast<int64_t>(l) * N + k1;
+    static_for<0, CT>([&](auto kc) __attribute__((always_inline)) {
+      constexpr int k = decltype(kc)::value;
+      const T p = POT ? vr[ST * k] : static_cast<T>(a.scale);
+      ua[k].re *= p;
+      ua[k].im *= p;
+      if constexpr (V == 2) {
+        ub[k].re *= p;
+        ub[k].im *= p;
+      }
+    });
+  };
+  using One = std::integral_constant<int, 1>;
+  using C1 = std::integral_constant<int, R1>;
+  using C2 = std::integral_constant<int, R2>;
+  cpx<T>* back = reinterpret_cast<cpx<T>*>(a.back);
 
   if constexpr (R2 == 1) {
     for (int it = threadIdx.x; it < items1; it += blockDim.x) {
       load(it);
+      const int l = pass_div(it, fc, inv_fc), f = it - l * fc;
       dft<R1, S>(va);
       if constexpr (V == 2) dft<R1, S>(vb);
-      const int l = pass_div(it, fc, inv_fc);
-      emit(it - l * fc, l, 0, va, vb, std::integral_constant<int, 1>{}, std::integral_constant<int, R1>{});
+      if (f >= nfl || l >= nl) continue;
+      if constexpr (POT || S < 0) weigh(l, 0, va, vb, One{}, C1{});
+      if constexpr (S > 0) emit_dense(f, l, 0, va, vb, One{}, C1{});
+      else emit_gather(dst, f, l, 0, va, vb, One{}, C1{});
+      if constexpr (POT) {
+        if (!back) continue;
+        dft<R1, -1>(va);
+        if constexpr (V == 2) dft<R1, -1>(vb);
+        emit_gather(back, f, l, 0, va, vb, One{}, C1{});
+      }
     }
     return;
   } else {
@@ -399,10 +423,6 @@ __global__ void __launch_bounds__(pass_max_threads(N, sizeof(T) * V == 4)) pass_
     const bool on2 = it < a.lines * R1 * fc;
     if (on1) {
       const TwEntry<T>* tr = tw + i1 * tw_row_stride(R1);
-      auto twiddle = [](cpx<T> x, const TwEntry<T>& e) __attribute__((always_inline)) {
-        if constexpr (std::is_same<T, float>::value) return cmul_hl(x, {e.re, e.im}, {e.lre, e.lim});
-        else return cmul(x, {e.re, e.im});
-      };
       dft<R1, S>(va);
       if constexpr (V == 2) {
         __builtin_amdgcn_sched_barrier(0);  // (one transform's temporaries at a time)
@@ -412,51 +432,92 @@ __global__ void __launch_bounds__(pass_max_threads(N, sizeof(T) * V == 4)) pass_
       static_for<1, R1>([&](auto kc) __attribute__((always_inline)) {
         constexpr int k = decltype(kc)::value;
         const TwEntry<T> e = tr[k];
-        va[k] = twiddle(va[k], e);
-        if constexpr (V == 2) vb[k] = twiddle(vb[k], e);
+        va[k] = twiddle(va[k], e, 1);
+        if constexpr (V == 2) vb[k] = twiddle(vb[k], e, 1);
       });
     }
-    Part* out = buf + (l1 * R1 * RS + i1) * fc + f;
-    const Part* in = buf + (l2 * R1 + k1) * RS * fc + f;
     cpx<T> ua[R2], ub[V == 2 ? R2 : 1];
-    if (on1) {
-      static_for<0, R1>([&](auto kc) __attribute__((always_inline)) {
-        constexpr int k = decltype(kc)::value;
-        if constexpr (V == 2) out[k * RS * fc] = Part{va[k].re, vb[k].re};
-        else out[k * RS * fc] = Part{va[k].re};
-      });
-    }
-    __syncthreads();
+    // rows of `from` values at out + k*step become rows of `to` values at in +
+    // i*fc, real parts first
+    auto exchange = [&](bool w, auto& xa, auto& xb, Part* out, int step, auto from_c, bool r, auto& ya,
+                        auto& yb, const Part* in, auto to_c) __attribute__((always_inline)) {
+      constexpr int FR = decltype(from_c)::value, TO = decltype(to_c)::value;
+      if (w)
+        static_for<0, FR>([&](auto kc) __attribute__((always_inline)) {
+          constexpr int k = decltype(kc)::value;
+          out[k * step] = parts<V>(xa[k].re, xb[V == 2 ? k : 0].re);
+        });
+      __syncthreads();
+      if (r)
+        static_for<0, TO>([&](auto ic) __attribute__((always_inline)) {
+          constexpr int i = decltype(ic)::value;
+          const Part x = in[i * fc];
+          ya[i].re = x[0];
+          if constexpr (V == 2) yb[i].re = x[1];
+        });
+      __syncthreads();
+      if (w)
+        static_for<0, FR>([&](auto kc) __attribute__((always_inline)) {
+          constexpr int k = decltype(kc)::value;
+          out[k * step] = parts<V>(xa[k].im, xb[V == 2 ? k : 0].im);
+        });
+      __syncthreads();
+      if (r)
+        static_for<0, TO>([&](auto ic) __attribute__((always_inline)) {
+          constexpr int i = decltype(ic)::value;
+          const Part x = in[i * fc];
+          ya[i].im = x[0];
+          if constexpr (V == 2) yb[i].im = x[1];
+        });
+    };
+    exchange(on1, va, vb, buf + (l1 * R1 * RS + i1) * fc + f, RS * fc, C1{}, on2, ua, ub,
+             buf + (l2 * R1 + k1) * RS * fc + f, C2{});
+    const bool live2 = on2 && f < nfl && l2 < nl;
     if (on2) {
-      static_for<0, R2>([&](auto ic) __attribute__((always_inline)) {
-        constexpr int i = decltype(ic)::value;
-        const Part x = in[i * fc];
-        ua[i].re = x[0];
-        if constexpr (V == 2) ub[i].re = x[1];
-      });
-    }
-    __syncthreads();
-    if (on1) {
-      static_for<0, R1>([&](auto kc) __attribute__((always_inline)) {
-        constexpr int k = decltype(kc)::value;
-        if constexpr (V == 2) out[k * RS * fc] = Part{va[k].im, vb[k].im};
-        else out[k * RS * fc] = Part{va[k].im};
-      });
-    }
-    __syncthreads();
-    if (on2) {
-      static_for<0, R2>([&](auto ic) __attribute__((always_inline)) {
-        constexpr int i = decltype(ic)::value;
-        const Part x = in[i * fc];
-        ua[i].im = x[0];
-        if constexpr (V == 2) ub[i].im = x[1];
-      });
       dft<R2, S>(ua);
       if constexpr (V == 2) {
         __builtin_amdgcn_sched_barrier(0);
         dft<R2, S>(ub);
       }
-      emit(f, l2, k1, ua, ub, std::integral_constant<int, R1>{}, std::integral_constant<int, R2>{});
+    }
+    if (live2) {
+      if constexpr (POT || S < 0) weigh(l2, k1, ua, ub, C1{}, C2{});
+      if constexpr (S > 0) emit_dense(f, l2, k1, ua, ub, C1{}, C2{});
+      else emit_gather(dst, f, l2, k1, ua, ub, C1{}, C2{});
+    }
+    if constexpr (POT) {
+      // the forward transform of the weighted row, back into its slab row: the
+      // same split with the stages' roles exchanged (R2 values at stride R1 in
+      // this thread), whose rows of R1 values take RS1 pieces
+      if (!back) return;
+      constexpr int RS1 = R1 | 1;
+      if (on2) {
+        const TwEntry<T>* tc = tw + k1;
+        dft<R2, -1>(ua);
+        if constexpr (V == 2) {
+          __builtin_amdgcn_sched_barrier(0);
+          dft<R2, -1>(ub);
+          __builtin_amdgcn_sched_barrier(0);
+        }
+        static_for<1, R2>([&](auto kc) __attribute__((always_inline)) {
+          constexpr int k = decltype(kc)::value;
+          const TwEntry<T> e = tc[k * tw_row_stride(R1)];
+          ua[k] = twiddle(ua[k], e, -1);
+          if constexpr (V == 2) ub[k] = twiddle(ub[k], e, -1);
+        });
+      }
+      __syncthreads();
+      cpx<T> wa[R1], wb[V == 2 ? R1 : 1];  // (va would stay live where on1 is false)
+      exchange(on2, ua, ub, buf + (l2 * R2 * RS1 + k1) * fc + f, RS1 * fc, C2{}, on1, wa, wb,
+               buf + (l1 * R2 + i1) * RS1 * fc + f, C1{});
+      if (on1 && f < nfl && l1 < nl) {
+        dft<R1, -1>(wa);
+        if constexpr (V == 2) {
+          __builtin_amdgcn_sched_barrier(0);
+          dft<R1, -1>(wb);
+        }
+        emit_gather(back, f, l1, i1, wa, wb, C2{}, C1{});
+      }
     }
   }
 }
@@ -475,12 +536,15 @@ __global__ void __launch_bounds__(pass_max_threads(N, sizeof(T) * V == 4)) pass_
   X(270) X(288) X(300) X(320) X(324) X(360) X(375) X(384) X(400) X(405) X(432) X(450) X(480) \
   X(486) X(500) X(512)
 
+// (S = +2: the x pass of the potential step)
 template <int S, typename T, int V, int N>
 hipError_t pass_one(const PassArgs& a, int threads, size_t lds, hipStream_t st, bool attr_only) {
+  constexpr int SG = S > 0 ? 1 : -1;
   if (attr_only)
-    return hipFuncSetAttribute(reinterpret_cast<const void*>(pass_kernel<S, T, V, N>),
+    return hipFuncSetAttribute(reinterpret_cast<const void*>(pass_kernel<SG, T, V, N, S == 2>),
                                hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(lds));
-  hipLaunchKernelGGL((pass_kernel<S, T, V, N>), dim3(pass_grid(a.total, a.group)), dim3(threads), lds, st, a);
+  hipLaunchKernelGGL((pass_kernel<SG, T, V, N, S == 2>), dim3(pass_grid(a.total, a.group)), dim3(threads),
+                     lds, st, a);
   return hipGetLastError();
 }
 

@@ -41,6 +41,8 @@ constexpr int pass_grid(int total, int group) {
 }
 
 enum { kPassZ = 0, kPassY = 1, kPassX = 2 };
+// (kPassPotential: the x pass that multiplies by V, with or without the way back)
+enum PassMode { kPassInverse, kPassForward, kPassPotential };
 // What a lane holds of a point: one complex64, two neighbouring bands of
 // complex64, one complex128 value.
 enum PassElem { kElemC64 = 0, kElemC64x2 = 1, kElemC128 = 2 };
@@ -78,7 +80,8 @@ struct PassArgs {
   const void *root, *root_lo;  // exp(-2*pi*i*j/n) (FP32: hi and lo)
   const void* src;
   void* dst;
-  const void* pot;     // x, inverse: real potential V[z][y][x] or null
+  const void* pot;     // potential x pass: V[z][y][x]
+  void* back;          // and the slab scratch its transform back goes to, or null
   double scale;        // z, forward: 1/N (1 elsewhere)
 };
 

@@ -13,6 +13,9 @@ FFTB_PASS_DECL(+1, float, 2)
 FFTB_PASS_DECL(-1, float, 2)
 FFTB_PASS_DECL(+1, double, 1)
 FFTB_PASS_DECL(-1, double, 1)
+FFTB_PASS_DECL(+2, float, 1)
+FFTB_PASS_DECL(+2, float, 2)
+FFTB_PASS_DECL(+2, double, 1)
 
 namespace {
 template <int S, typename T, int V>
@@ -34,17 +37,19 @@ hipError_t dispatch(PassElem el, int n, const PassArgs& a, int threads, size_t l
 }
 }  // namespace
 
-hipError_t launch_pass(bool inverse, PassElem el, int n, const PassArgs& a, int threads, size_t lds,
+hipError_t launch_pass(PassMode mode, PassElem el, int n, const PassArgs& a, int threads, size_t lds,
                        hipStream_t st) {
-  return inverse ? dispatch<+1>(el, n, a, threads, lds, st, false)
-                 : dispatch<-1>(el, n, a, threads, lds, st, false);
+  return mode == kPassInverse   ? dispatch<+1>(el, n, a, threads, lds, st, false)
+         : mode == kPassForward ? dispatch<-1>(el, n, a, threads, lds, st, false)
+                                : dispatch<+2>(el, n, a, threads, lds, st, false);
 }
 
 // Allow the kernels of length n `lds` bytes of dynamic LDS.
-hipError_t prepare_pass(bool inverse, PassElem el, int n, size_t lds) {
+hipError_t prepare_pass(PassMode mode, PassElem el, int n, size_t lds) {
   PassArgs a{};
-  return inverse ? dispatch<+1>(el, n, a, 0, lds, nullptr, true)
-                 : dispatch<-1>(el, n, a, 0, lds, nullptr, true);
+  return mode == kPassInverse   ? dispatch<+1>(el, n, a, 0, lds, nullptr, true)
+         : mode == kPassForward ? dispatch<-1>(el, n, a, 0, lds, nullptr, true)
+                                : dispatch<+2>(el, n, a, 0, lds, nullptr, true);
 }
 
 }  // namespace fftb

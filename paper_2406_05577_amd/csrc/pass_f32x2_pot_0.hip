@@ -1,0 +1,6 @@
+// Axis-pass kernels: complex64, two bands per lane, x pass of the potential step, lengths of part 0.
+#include "kernels_pass.hpp"
+
+namespace fftb {
+FFTB_PASS_INST(, 2, float, 2, 0)
+}  // namespace fftb

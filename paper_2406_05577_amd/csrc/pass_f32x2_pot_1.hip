@@ -1,0 +1,6 @@
+// Axis-pass kernels: complex64, two bands per lane, x pass of the potential step, lengths of part 1.
+#include "kernels_pass.hpp"
+
+namespace fftb {
+FFTB_PASS_INST(, 2, float, 2, 1)
+}  // namespace fftb

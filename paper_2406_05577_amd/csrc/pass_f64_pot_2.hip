@@ -1,0 +1,6 @@
+// Axis-pass kernels: complex128, x pass of the potential step, lengths of part 2.
+#include "kernels_pass.hpp"
+
+namespace fftb {
+FFTB_PASS_INST(, 2, double, 1, 2)
+}  // namespace fftb

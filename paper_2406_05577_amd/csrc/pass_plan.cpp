@@ -25,7 +25,9 @@ bool make_tile(int n, int es, int64_t nf, int nrows, bool even, bool ragged, Pas
   const int r2 = n / r1, m = r2 == 1 ? 1 : std::max(r1, r2);
   int target = std::max(1, 256 / (m * w)) * w;
   const auto lds_of = [&](int fc, int lines) {
-    return r2 > 1 ? static_cast<size_t>(lines) * fc * r1 * (r2 | 1) * (es / 2) : size_t{0};
+    // (the larger of the two exchanges of the potential's x pass)
+    const int rows = std::max(r1 * (r2 | 1), r2 * (r1 | 1));
+    return r2 > 1 ? static_cast<size_t>(lines) * fc * rows * (es / 2) : size_t{0};
   };
   const size_t tab = r2 > 1 ? static_cast<size_t>(r1 | 1) * r2 * 16 : 0;
   while (target > w && lds_of(target, 1) + tab > kPassLdsMax / 2) target -= w;

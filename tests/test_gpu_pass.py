@@ -141,3 +141,30 @@ def test_pass_repeats(dtype):
         assert all(torch.equal(torch.view_as_real(a), torch.view_as_real(b))
                    for a, b in zip(results(), first))
     p.close()
+
+
+@pytest.mark.parametrize("dtype", ["c128", "c64"])
+@pytest.mark.parametrize("i", range(len(SHAPES)))
+def test_pass_potential(i, dtype):
+    """The potential step's x pass (both transforms of a row in one workgroup)
+    against the two directions run one after the other, which the oracle checks."""
+    import torch
+    dims, nk, nb = SHAPES[i]
+    w = _workload(dims, nk, nb, dtype, 500 + i)
+    sph = torch.from_numpy(w.sphere_concat()).to("cuda").to(
+        torch.complex128 if dtype == "c128" else torch.complex64)
+    p = make_plan(w, dtype=dtype, flags=(0, 4)[i % 2])
+    v = torch.rand(dims[0] * dims[1] * dims[2], dtype=sph.real.dtype, device="cuda") - 0.25
+    g = torch.full((p.info["grid_elems"],), complex(float("nan"), 0.0), dtype=sph.dtype, device="cuda")
+    out = torch.full_like(sph, complex(float("nan"), 0.0))
+    for _ in range(2):
+        p.apply_potential(sph, v, g, out)
+    want = p.sphere_to_grid(sph)
+    at = 0
+    for s in w.spheres:
+        n = v.numel() * s.nbands
+        want[at:at + n] *= v.repeat_interleave(s.nbands)
+        at += n
+    assert rel(g.cpu().numpy(), want.cpu().numpy()) <= TOL[dtype]
+    assert rel(out.cpu().numpy(), p.grid_to_sphere(want).cpu().numpy()) <= TOL[dtype]
+    p.close()
