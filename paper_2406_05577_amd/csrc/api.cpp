@@ -165,6 +165,9 @@ struct fftb_plan_s {
     std::array<const void*, 4> key = {};  // the buffers it was captured for
   } gc[3];
   hipStream_t cap_stream = nullptr;
+  // the second stream of the plane groups (null: one stream), and its fork and join
+  hipStream_t side = nullptr;
+  hipEvent_t side_go = nullptr, side_done = nullptr;
   bool uses_pass() const { return dir[0].pass || dir[1].pass; }
   bool uses_classes() const { return !dir[0].pass || !dir[1].pass; }
   // elements of the scratch d_col: the class-split regions of the directions
@@ -195,6 +198,9 @@ struct fftb_plan_s {
       if (g.graph) (void)hipGraphDestroy(g.graph);
     }
     if (cap_stream) (void)hipStreamDestroy(cap_stream);
+    if (side) (void)hipStreamDestroy(side);
+    if (side_go) (void)hipEventDestroy(side_go);
+    if (side_done) (void)hipEventDestroy(side_done);
     for (auto& b : bufs)
       if (b.p) (void)hipFree(b.p);
   }
@@ -1101,6 +1107,12 @@ fftb_status device_setup(fftb_plan_s& P, hipStream_t st) {
           return fail(FFTB_ERR_HIP, std::string("hipFuncSetAttribute: ") + hipGetErrorString(e));
       }
     }
+    if (P.pp.two_streams()) {
+      if ((e = hipStreamCreateWithFlags(&P.side, hipStreamNonBlocking)) != hipSuccess ||
+          (e = hipEventCreateWithFlags(&P.side_go, hipEventDisableTiming)) != hipSuccess ||
+          (e = hipEventCreateWithFlags(&P.side_done, hipEventDisableTiming)) != hipSuccess)
+        return fail(FFTB_ERR_HIP, std::string("second stream: ") + hipGetErrorString(e));
+    }
   }
   for (auto& D : P.dir) {
     if (D.pass) continue;
@@ -1299,10 +1311,11 @@ hipError_t enqueue(fftb_plan_s* P, const KArgs& a, const DirCfg& D, bool inverse
 
 // Enqueue axis passes: the z pass over all columns, and the y and x passes over
 // groups of planes whose slab scratch stays in the last-level cache between
-// them. `inverse` writes the grid (times `pot` if given), `forward` reads it; both
-// (the potential step): the x pass transforms its rows back into the slab scratch
-// and the grid is not read. The planes of a direction take the profile slot of
-// its plane kernel (the potential step's that of the inverse).
+// them, half of the planes on the plan's second stream if it has one.
+// `inverse` writes the grid (times `pot` if given), `forward` reads it; both (the
+// potential step): the x pass transforms its rows back into the slab scratch and
+// the grid is not read. The planes of a direction take the profile slot of its
+// plane kernel (the potential step's that of the inverse).
 hipError_t enqueue_pass(fftb_plan_s* P, bool inverse, bool forward, const void* in, void* grid, void* out,
                         const void* pot, void* col, hipStream_t st, bool profile) {
   const PassPlan& pp = P->pp;
@@ -1316,6 +1329,7 @@ hipError_t enqueue_pass(fftb_plan_s* P, bool inverse, bool forward, const void* 
   base.splane = pp.splane;
   base.sph = P->d_psph;
   base.scale = 1.0;
+  hipStream_t on = st;
   auto launch = [&](int kind, bool inv, int p0, int np) {
     PassArgs a = base;
     const PassTile& t = kind == kPassZ ? pp.tz : kind == kPassY ? pp.ty : pp.tx;
@@ -1368,7 +1382,7 @@ hipError_t enqueue_pass(fftb_plan_s* P, bool inverse, bool forward, const void* 
     }
     a.src = inv ? gat : den;
     a.dst = const_cast<void*>(inv ? den : gat);
-    return launch_pass(mode, pp.elem, n, a, t.threads, t.lds, st);
+    return launch_pass(mode, pp.elem, n, a, t.threads, t.lds, on);
   };
   auto timed = [&](int kid, auto&& body) {
     hipEvent_t ea = nullptr, eb = nullptr;
@@ -1385,15 +1399,35 @@ hipError_t enqueue_pass(fftb_plan_s* P, bool inverse, bool forward, const void* 
     }
     return e;
   };
+  auto group = [&](int p0, int np) {
+    hipError_t e = inverse ? launch(kPassY, true, p0, np) : hipSuccess;
+    if (e == hipSuccess) e = launch(kPassX, inverse, p0, np);
+    if (e == hipSuccess && forward) e = launch(kPassY, false, p0, np);
+    return e;
+  };
   auto planes = [&] {
-    for (int p0 = 0; p0 < pp.nplanes; p0 += pp.group) {
-      const int np = std::min(pp.group, pp.nplanes - p0);
-      hipError_t e = inverse ? launch(kPassY, true, p0, np) : hipSuccess;
-      if (e == hipSuccess) e = launch(kPassX, inverse, p0, np);
-      if (e == hipSuccess && forward) e = launch(kPassY, false, p0, np);
-      if (e != hipSuccess) return e;
+    hipError_t e = hipSuccess;
+    if (!P->side) {
+      for (int p0 = 0; p0 < pp.nplanes && e == hipSuccess; p0 += pp.group)
+        e = group(p0, std::min(pp.group, pp.nplanes - p0));
+      return e;
     }
-    return hipSuccess;
+    // half of the planes on each stream, in groups of half the size
+    const int half = (pp.nplanes + 1) / 2, g = pp.group / 2;
+    char* slabs = static_cast<char*>(slab);
+    if ((e = hipEventRecord(P->side_go, st)) != hipSuccess) return e;
+    if ((e = hipStreamWaitEvent(P->side, P->side_go, 0)) != hipSuccess) return e;
+    for (int i = 0; i < half && e == hipSuccess; i += g)
+      for (int w = 0; w < 2 && e == hipSuccess; ++w) {
+        const int p0 = w * half + i, np = std::min({g, half - i, pp.nplanes - p0});
+        on = w ? P->side : st;
+        slab = slabs + static_cast<size_t>(w) * g * pp.splane * es;
+        if (np > 0) e = group(p0, np);
+      }
+    on = st;
+    const hipError_t r = hipEventRecord(P->side_done, P->side);
+    const hipError_t j = r == hipSuccess ? hipStreamWaitEvent(st, P->side_done, 0) : r;
+    return e != hipSuccess ? e : j;
   };
   hipError_t e = hipSuccess;
   if (inverse) e = timed(0, [&] { return launch(kPassZ, true, 0, 0); });
@@ -1514,8 +1548,9 @@ void log_plan(const fftb_plan_s& P) {
                  D.fold_m);
     // the axis passes the direction takes instead
     if (D.pass) {
-      std::fprintf(stderr, "  %s: axis passes, %d groups of %d planes", d == 0 ? "inverse" : "forward",
-                   (P.pp.nplanes + P.pp.group - 1) / P.pp.group, P.pp.group);
+      std::fprintf(stderr, "  %s: axis passes, %d groups of %d planes%s", d == 0 ? "inverse" : "forward",
+                   (P.pp.nplanes + P.pp.group - 1) / P.pp.group, P.pp.group,
+                   P.pp.two_streams() ? " halved on two streams" : "");
       const char* name[3] = {"z", "y", "x"};
       const PassTile* tl[3] = {&P.pp.tz, &P.pp.ty, &P.pp.tx};
       const int n[3] = {P.nz, P.ny, P.nx};

@@ -106,6 +106,13 @@ struct PassPlan {
   int64_t splane = 0;     // slab scratch values per plane
   int64_t col_elems = 0;  // column scratch values
   int64_t s_elems() const { return splane * group; }
+  // Four groups or more: the planes on two streams, each with half of the slab
+  // scratch, so that the end of a launch overlaps the other stream's launches
+  // (256^3, 24 complex128 bands, a round trip 5.41 -> 5.15 ms; 144x160x180, 128
+  // bands, the potential step 5.38 -> 5.19 ms; 128^3, 256 complex64 bands, forward
+  // 1.82 -> 1.74 ms). Fewer lose by the smaller launches (108x100x120, 50 complex64
+  // bands, two groups: 0.497 -> 0.507 ms).
+  bool two_streams() const { return group >= 2 && nplanes > 3 * group; }
 };
 
 // Build the pass plan; false where a length has no split or a size does not

@@ -168,3 +168,51 @@ def test_pass_potential(i, dtype):
     assert rel(g.cpu().numpy(), want.cpu().numpy()) <= TOL[dtype]
     assert rel(out.cpu().numpy(), p.grid_to_sphere(want).cpu().numpy()) <= TOL[dtype]
     p.close()
+
+
+@pytest.mark.parametrize("dtype", ["c128", "c64"])
+@pytest.mark.parametrize("mode", ["plain", "stream", "graph", "capture"])
+def test_pass_two_streams(mode, dtype, capfd, monkeypatch):
+    """The planes on two streams: the same bits as on one, on the caller's
+    stream, replayed and captured, with the caller's work queued behind each
+    call (a spoiled or freed buffer shows a missing wait)."""
+    import torch
+    w = synth.small_workload((80, 72, 60), (5, 5, 5), [(0.1, 0.2, -0.3), (0, 0, 0)], 12, seed=91, dtype=dtype)
+    sph = to_device(np.concatenate([c.reshape(-1) for c in w.coeffs]), dtype)
+    v = torch.rand(80 * 72 * 60, dtype=sph.real.dtype, device="cuda") - 0.5
+    one = make_plan(w, dtype=dtype)
+    want = one.sphere_to_grid(sph)
+    back = one.grid_to_sphere(want)
+    vg = torch.empty_like(want)
+    vout = one.apply_potential(sph, v, vg)
+    monkeypatch.setenv("FFTB_LOG", "1")
+    monkeypatch.setenv("FFTB_MAX_DEVICE_BYTES", str(1 << 30))   # (small groups)
+    p = make_plan(w, dtype=dtype, flags=4 if mode == "graph" else 0)
+    assert "on two streams" in capfd.readouterr().err
+    monkeypatch.delenv("FFTB_MAX_DEVICE_BYTES")
+    s_in, g, s, pg, po = sph.clone(), torch.empty_like(want), torch.empty_like(sph), torch.empty_like(want), torch.empty_like(sph)
+
+    def step():
+        p.sphere_to_grid(s_in, g)
+        p.grid_to_sphere(g, s)
+        p.apply_potential(s_in, v, pg, po)
+
+    st = torch.cuda.Stream() if mode != "plain" else torch.cuda.current_stream()
+    st.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(st):
+        if mode == "capture":
+            graph = torch.cuda.CUDAGraph()
+            with torch.cuda.graph(graph, stream=st):
+                step()
+            step = graph.replay
+        for _ in range(5):
+            for t in (g, s, pg, po):
+                t.fill_(float("nan"))
+            s_in.copy_(sph)
+            step()
+            s_in.fill_(float("nan"))
+            for t, r in ((g, want), (s, back), (pg, vg), (po, vout)):
+                assert torch.equal(t, r)
+    torch.cuda.synchronize()
+    p.close()
+    one.close()
