@@ -771,10 +771,26 @@ fftb_status choose_tiling(fftb_plan_s& P, int d, const fftb_dir_tuning& t) {
 //   scratch of a plane group stays in the last-level cache (144x160x180, 128
 //   complex128 bands: 4.41 -> 3.55 ms; 96^3, 8 x 64 complex64 bands: 1.83 -> 1.62
 //   ms; 128^3, 256 complex64 bands: 2.17 -> 1.98 ms);
-// - inverse with too few plane tasks to fill the 256 CUs (32^3, 4 complex128
-//   bands, 32 tasks: 23 -> 17 us; with 512 tasks, 256 complex64 bands, the class
-//   pairs are faster: 39 against 45 us, as they are on every larger grid:
-//   144x160x180 3.28 against 3.61 ms).
+// - inverse unless the class pairs (one read of a plane's columns per two y
+//   classes) have whole work: 96-point z lines, class pairs -> passes,
+//   - odd class counts have no pairs (144^2, 48 complex128 bands: 0.69 -> 0.64 ms,
+//     96 complex64: 0.97 -> 0.63);
+//   - band chunks that are not full make the same work for fewer bands, unaligned
+//     (128^2, 24 complex64 bands: 153 -> 137 us, 18: 260 -> 111, 54 complex128
+//     bands: 0.98 -> 0.66 ms; 56, which fill them, 0.53 -> 0.61);
+//   - complex64 with more than 8 classes re-reads the columns too often (96x192,
+//     112 bands: 0.74 -> 0.69 ms, 144x160 80: 0.64 -> 0.62; 128^2 112: 0.58 ->
+//     0.62), complex128 only on x lines of 144 points and where the columns are many
+//     (144x160x180, 4 x 32 bands 3.73 -> 3.19 ms, 16 bands 232 -> 256 us; 128x192,
+//     40 bands 0.62 -> 0.66 ms);
+//   - complex64 z lines of 144 and 160 points: the class columns' 36x4 and 40x4
+//     lines take 2.5 times the z pass (128x96x160, 4 x 64 bands, 497 against 203
+//     us; the inverse 1.83 -> 1.61 ms, 144^3 2.61 -> 2.19; 180: 247 against 221);
+//   - too few plane tasks for the 256 CUs, one workgroup each (32^3, 4 complex128
+//     bands, 32 tasks: 23 -> 17 us), or a last round of them mostly empty: 576
+//     tasks, 96^2, 32 complex64 bands 118 -> 99 us, 16 complex128 bands 101 -> 97;
+//     384 tasks, 128x64, 98 -> 90, but 84 -> 88 in complex128; 768, 128^2, 166 ->
+//     174 and 136 -> 173.
 fftb_status choose_dir(fftb_plan_s& P, int d, const fftb_dir_tuning& t) {
   DirCfg& D = P.dir[d];
   D.pass = D.untuned = false;
@@ -785,10 +801,18 @@ fftb_status choose_dir(fftb_plan_s& P, int d, const fftb_dir_tuning& t) {
   if (!D.untuned || (P.flags & FFTB_PLAN_MFMA) || P.nx > kPassMaxN ||
       P.ny > kPassMaxN || P.nz > kPassMaxN)
     return FFTB_OK;
+  const bool fp64 = P.dtype == FFTB_C128;
+  bool pairs = d == 0 && D.bil2 && D.qc == 2;
   int64_t tasks = 0;
-  for (const auto& s : P.sph)
+  for (const auto& s : P.sph) {
+    pairs = pairs && s.nb % D.bc == 0;
     tasks += static_cast<int64_t>(P.nz) * ((s.nb + D.bc - 1) / D.bc) * (D.n1 / D.qc);
-  D.pass = !D.bil2 || d == 1 || tasks < 256;
+  }
+  const int64_t rounds = (tasks + 255) / 256;
+  if (tasks < 256 || (5 * tasks < 4 * 256 * rounds && (!fp64 || D.n1 >= 6))) pairs = false;
+  if (fp64 ? P.nx == 144 && D.n1 > 8 && tasks >= 2048 : D.n1 > 8 || P.nz == 144 || P.nz == 160)
+    pairs = false;
+  D.pass = !pairs;
   return FFTB_OK;
 }
 

@@ -38,8 +38,9 @@ def _log(capfd, dims, nb, dtype="c128", flags=0, tuning=None):
 
 
 def test_which_plans_take_passes(monkeypatch, capfd):
-    """Passes: no tiling request, and no band-inner x lines, the forward, or too
-    few inverse tasks; every other direction keeps the class-split kernels."""
+    """Passes: no tiling request, and no band-inner x lines, the forward, or an
+    inverse whose class pairs have no whole work; every other direction keeps the
+    class-split kernels."""
     monkeypatch.setenv("FFTB_LOG", "1")
     for dtype in ("c128", "c64"):
         p, log = _log(capfd, (60, 50, 45), 7, dtype)
@@ -51,12 +52,16 @@ def test_which_plans_take_passes(monkeypatch, capfd):
         # lines longer than any split, and band-inner shapes
         _, log = _log(capfd, (6, 4, 540), 3, dtype)
         assert "axis passes" not in log
-        # band-inner shapes: the forward, and an inverse of fewer tasks than CUs
-        p, log = _log(capfd, (96, 96, 96), 7, dtype)
-        assert p.info["tuning"]["inv"]["path"] == 3 and "forward: axis passes" in log
-        assert "inverse: axis passes" not in log
-        _, log = _log(capfd, (32, 32, 32), 7, dtype)
-        assert log.count("axis passes") == 2
+        # band-inner shapes: the forward, and the inverse unless its class pairs fill
+        # their band chunks (8 bands, complex64 16) and the rounds of 256 tasks
+        for dims, nb, pairs in (((96, 96, 96), 64, True), ((96, 96, 96), 63, False),
+                                ((96, 96, 96), 72, dtype == "c128"), ((32, 32, 32), 8, False),
+                                ((96, 96, 96), 16, False), ((96, 144, 96), 64, False),
+                                ((128, 128, 128), 64, True), ((144, 160, 180), 128, False),
+                                ((144, 160, 180), 16, dtype == "c128"), ((96, 96, 160), 64, dtype == "c128")):
+            p, log = _log(capfd, dims, nb, dtype)
+            assert p.info["tuning"]["inv"]["path"] == 3 and "forward: axis passes" in log
+            assert ("inverse: axis passes" not in log) == pairs, (dims, nb)
         _, log = _log(capfd, (96, 96, 96), 7, dtype, tuning=dict(path=3))
         assert "axis passes" not in log
 
