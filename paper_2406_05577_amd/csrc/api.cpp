@@ -46,6 +46,8 @@ hipError_t launch_zero_scratch(void* p, size_t bytes, hipStream_t st);
 hipError_t launch_pass(PassMode mode, PassElem el, int n, const PassArgs& a, int threads, size_t lds,
                        hipStream_t st);
 hipError_t prepare_pass(PassMode mode, PassElem el, int n, size_t lds);
+hipError_t launch_plane(PassMode mode, PassElem el, const PlaneArgs& a, int threads, size_t lds, hipStream_t st);
+hipError_t prepare_plane(PassMode mode, PassElem el, size_t lds);
 }  // namespace fftb
 
 using namespace fftb;
@@ -1131,6 +1133,10 @@ fftb_status device_setup(fftb_plan_s& P, hipStream_t st) {
           return fail(FFTB_ERR_HIP, std::string("hipFuncSetAttribute: ") + hipGetErrorString(e));
       }
     }
+    if (P.pp.plane.on)
+      for (PassMode m : {kPassInverse, kPassForward, kPassPotential})
+        if ((e = prepare_plane(m, P.pp.elem, P.pp.plane.lds)) != hipSuccess)
+          return fail(FFTB_ERR_HIP, std::string("hipFuncSetAttribute: ") + hipGetErrorString(e));
     if (P.pp.two_streams()) {
       if ((e = hipStreamCreateWithFlags(&P.side, hipStreamNonBlocking)) != hipSuccess ||
           (e = hipEventCreateWithFlags(&P.side_go, hipEventDisableTiming)) != hipSuccess ||
@@ -1431,6 +1437,34 @@ hipError_t enqueue_pass(fftb_plan_s* P, bool inverse, bool forward, const void* 
   };
   auto planes = [&] {
     hipError_t e = hipSuccess;
+    if (pp.plane.on) {
+      const PlaneTile& t = pp.plane;
+      PlaneArgs a = {};
+      a.nx = P->nx;
+      a.ny = P->ny;
+      a.nz = P->nz;
+      a.r1x = pass_r1(P->nx);
+      a.r1y = pass_r1(P->ny);
+      a.tiles = t.tiles;
+      a.fc = t.fc;
+      a.total = pp.nplanes * t.tiles;
+      a.lds_twx = t.lds_twx;
+      a.lds_twy = t.lds_twy;
+      a.lds_x = t.lds_x;
+      a.sph = P->d_psph;
+      a.colidx = P->d_pcolidx;
+      a.xinv = P->d_pxinv;
+      a.rootx = P->d_rootx;
+      a.rootx_lo = P->d_rootx_lo;
+      a.rooty = P->d_twf;
+      a.rooty_lo = P->d_twf_lo;
+      a.col_in = col;
+      a.col_out = forward ? col : nullptr;
+      a.grid = grid;
+      a.pot = pot;
+      const PassMode mode = !inverse ? kPassForward : pot ? kPassPotential : kPassInverse;
+      return launch_plane(mode, pp.elem, a, t.threads, t.lds, st);
+    }
     if (!P->side) {
       for (int p0 = 0; p0 < pp.nplanes && e == hipSuccess; p0 += pp.group)
         e = group(p0, std::min(pp.group, pp.nplanes - p0));
@@ -1581,6 +1615,8 @@ void log_plan(const fftb_plan_s& P) {
       for (int i = 0; i < 3; ++i)
         std::fprintf(stderr, ", %s %dx%d tile %d elements x %d rows, %d threads, LDS %zu B", name[i],
                      pass_r1(n[i]), n[i] / pass_r1(n[i]), tl[i]->fc, tl[i]->lines, tl[i]->threads, tl[i]->lds);
+      if (P.pp.plane.on)
+        std::fprintf(stderr, ", planes in one launch, %d elements, LDS %zu B", P.pp.plane.fc, P.pp.plane.lds);
       std::fprintf(stderr, "\n");
     }
   }

@@ -36,6 +36,9 @@ constexpr int pass_max_threads(int n, bool small) {
   return small || pass_r1(n) <= 12 ? 1024 : 512;
 }
 // Blocks of a launch whose tiles go to the XCDs in runs of `group`.
+// Longest x and y lines of the plane kernel: second factors of at most 8.
+constexpr int kPlaneMaxN = 64;
+
 constexpr int pass_grid(int total, int group) {
   return (total + 8 * group - 1) / (8 * group) * (8 * group);
 }
@@ -85,6 +88,21 @@ struct PassArgs {
   double scale;        // z, forward: 1/N (1 elsewhere)
 };
 
+struct PlaneArgs {
+  int nx, ny, nz;
+  int r1x, r1y;        // first factors of the axes' splits
+  int tiles, fc;       // a tile: one plane of fc elements
+  int total;           // tiles of the launch
+  int lds_twx, lds_twy, lds_x;  // byte offsets in LDS: twiddles, slab tables
+  const PassSph* sph;
+  const int32_t *colidx, *xinv;
+  const void *rootx, *rootx_lo, *rooty, *rooty_lo;
+  const void* col_in;
+  void* col_out;       // (potential: null without the way back)
+  void* grid;
+  const void* pot;
+};
+
 // ---- host side -------------------------------------------------------------
 struct PassTile {
   int fc = 0, lines = 1, threads = 64;
@@ -95,7 +113,16 @@ struct PassTile {
   bool tab_lds = false;
 };
 
+// The plane kernel's tile (on: the planes run as one launch of it).
+struct PlaneTile {
+  bool on = false;
+  int fc = 0, threads = 0, tiles = 0;
+  size_t lds = 0;
+  int lds_twx = 0, lds_twy = 0, lds_x = 0;
+};
+
 struct PassPlan {
+  PlaneTile plane;
   std::vector<PassSph> sph;
   std::vector<int32_t> gidx, colidx, xinv;
   PassTile tz, ty, tx;

@@ -74,6 +74,38 @@ void stage_tables(int n, int64_t lines, int64_t span, PassTile& t) {
   t.lds += b;
 }
 
+// The plane kernel's tile for planes of nx x ny points, if it serves them: at most
+// one 128-byte line of elements, fewer where the planes alone are few workgroups
+// for the 256 CUs, and all workgroups resident at once or nearly (a round trip,
+// passes -> plane kernel: 32^3, 4 complex128 bands, 128 workgroups of one element
+// 26.5 -> 22.3 us, 24.0 in 32 of four; 36x40x45, 20 bands, 225 workgroups 45 -> 35;
+// 32^3, 64 bands, 256 of 128 KB 48 -> 46; more than that gains nothing: 32^3, 256
+// bands, 1024: 116 -> 117; 48^3, 64 complex64 bands, 384 of 147 KB: 69 -> 77;
+// 36x40x45, 200 complex128 bands, 2250: 181 -> 220).
+void make_plane(int nx, int ny, int es, int64_t nel, int64_t nplanes, PlaneTile& t) {
+  if (nx > kPlaneMaxN || ny > kPlaneMaxN) return;
+  const auto tab = [](int n) {
+    const int r1 = pass_r1(n);
+    return static_cast<size_t>(r1 | 1) * (n / r1) * 16;
+  };
+  const size_t pts = static_cast<size_t>(nx) * ny * es;
+  const size_t tables = tab(nx) + tab(ny) + 8 * static_cast<size_t>(nx) + 16;
+  const auto blocks = [&](int fc) { return nplanes * ((nel + fc - 1) / fc); };
+  int fc = static_cast<int>(std::min<int64_t>(nel, 128 / es));
+  while (fc > 1 && (blocks(fc) < 192 || pts * fc + tables > kPassLdsMax)) fc = (fc + 1) / 2;
+  t.fc = fc;
+  t.tiles = static_cast<int>((nel + fc - 1) / fc);
+  t.lds_twx = static_cast<int>((pts * fc + 15) & ~size_t{15});
+  t.lds_twy = t.lds_twx + static_cast<int>(tab(nx));
+  t.lds_x = t.lds_twy + static_cast<int>(tab(ny));
+  t.lds = t.lds_x + 8 * static_cast<size_t>(nx);
+  const int items = fc * std::max(ny * std::max(pass_r1(nx), nx / pass_r1(nx)),
+                                  nx * std::max(pass_r1(ny), ny / pass_r1(ny)));
+  t.threads = std::min(512, (items + 63) / 64 * 64);
+  const int64_t resident = std::min<int64_t>(kPassLdsMax / t.lds, 2048 / t.threads);
+  t.on = blocks(fc) <= 320 * resident;
+}
+
 }  // namespace
 
 bool build_pass_plan(int nx, int ny, int nz, bool fp64, const std::vector<SphereTables>& sph,
@@ -173,6 +205,7 @@ bool build_pass_plan(int nx, int ny, int nz, bool fp64, const std::vector<Sphere
     d.ztile = P.ztotal;
     P.ztotal += static_cast<int>((static_cast<int64_t>(d.ncol) * d.nel + P.tz.fc - 1) / P.tz.fc);
   }
+  make_plane(nx, ny, es, max_nel, P.nplanes, P.plane);
   // equal groups of planes within the budget
   const int64_t most = std::max<int64_t>(1, s_budget / (P.splane * cs));
   const int64_t groups = (P.nplanes + most - 1) / most;

@@ -148,6 +148,17 @@ static void check(std::mt19937& g, int nx, int ny, int nz, bool fp64, const std:
   CHECK(build_pass_plan(nx, ny, nz, fp64, sph, row_max, budget, P));
   if (failures) return;
   CHECK(P.nplanes == nz * static_cast<int>(nbs.size()) && P.group >= 1);
+  if (P.plane.on) {
+    const PlaneTile& t = P.plane;
+    int nel = 0;
+    for (const PassSph& d : P.sph) nel = std::max(nel, d.nel);
+    const auto tab = [](int n) { return (pass_r1(n) | 1) * (n / pass_r1(n)) * 16; };
+    CHECK(nx <= kPlaneMaxN && ny <= kPlaneMaxN && t.fc >= 1 && t.fc * t.tiles >= nel);
+    CHECK(t.threads >= 64 && t.threads <= 512 && t.threads % 64 == 0);
+    CHECK(t.lds_twx >= nx * ny * t.fc * (P.elem == kElemC64 ? 8 : 16) && t.lds_twx % 16 == 0);
+    CHECK(t.lds_twy >= t.lds_twx + tab(nx) && t.lds_x >= t.lds_twy + tab(ny));
+    CHECK(static_cast<int>(t.lds) >= t.lds_x + 8 * nx && t.lds <= 160 * 1024 - 1024);
+  }
   int64_t cols = 0, slabs = 0, colrows = 0;
   for (size_t i = 0; i < sph.size(); ++i) {
     cols += static_cast<int64_t>(sph[i].ncol) * P.sph[i].nb * nz;

@@ -216,3 +216,47 @@ def test_pass_two_streams(mode, dtype, capfd, monkeypatch):
     torch.cuda.synchronize()
     p.close()
     one.close()
+
+
+PLANE_LENGTHS = [1, 2, 3, 4, 5, 6, 8, 9, 10, 12, 15, 16, 18, 20, 24, 25, 27, 30, 32, 36, 40, 45, 48, 50, 54, 60, 64]
+
+
+@pytest.mark.parametrize("dtype", ["c128", "c64"])
+@pytest.mark.parametrize("i", range(len(PLANE_LENGTHS)))
+def test_plane_kernel(i, dtype, capfd, monkeypatch):
+    """Planes in one launch: every length on both axes, whole and cut band tiles,
+    spheres of other band counts, both directions against the oracle and the
+    potential step against them."""
+    import torch
+    from paper_2406_05577_amd import Plan
+    dims = (PLANE_LENGTHS[i], PLANE_LENGTHS[(7 * i + 5) % len(PLANE_LENGTHS)], 3 + i % 3)
+    nbs = [((1, 4), (3, 6), (16, 10), (33, 2))[i % 4], (2,)][i % 5 == 4]
+    ws = [_workload(dims, 1, nb, dtype, 700 + 10 * i + s) for s, nb in enumerate(nbs)]
+    monkeypatch.setenv("FFTB_LOG", "1")
+    p = Plan(dims, [w.spheres[0].lin for w in ws], list(nbs), dtype=dtype, flags=(0, 4)[i % 2])
+    assert capfd.readouterr().err.count("planes in one launch") == 2
+    tdt = torch.complex128 if dtype == "c128" else torch.complex64
+    sph = to_device(np.concatenate([w.coeffs[0].reshape(-1) for w in ws]), dtype)
+    nan = complex(float("nan"), 0.0)
+    g = torch.full((p.info["grid_elems"],), nan, dtype=tdt, device="cuda")
+    back = torch.full_like(sph, nan)
+    for _ in range(2):
+        p.sphere_to_grid(sph, g)
+        p.grid_to_sphere(g, back)
+    n = dims[0] * dims[1] * dims[2]
+    v = torch.rand(n, dtype=g.real.dtype, device="cuda") - 0.25
+    want, at, soff = g.clone(), 0, 0
+    for w, nb in zip(ws, nbs):
+        s = w.spheres[0]
+        c = sph[soff:soff + s.ns * nb].cpu().numpy().reshape(s.ns, nb).astype(np.complex128)
+        got = g[at:at + n * nb].cpu().numpy()
+        assert rel(got, oracle.sphere_to_grid(dims, s.lin, c).ravel()) <= TOL[dtype], (dims, nb)
+        assert rel(back[soff:soff + s.ns * nb].cpu().numpy(), c.ravel()) <= TOL[dtype], (dims, nb)
+        want[at:at + n * nb] *= v.repeat_interleave(nb)
+        at, soff = at + n * nb, soff + s.ns * nb
+    pg, out = torch.full_like(g, nan), torch.full_like(sph, nan)
+    for _ in range(2):
+        p.apply_potential(sph, v, pg, out)
+    assert rel(pg.cpu().numpy(), want.cpu().numpy()) <= TOL[dtype]
+    assert rel(out.cpu().numpy(), p.grid_to_sphere(want).cpu().numpy()) <= TOL[dtype]
+    p.close()
