@@ -80,7 +80,8 @@ enum {
                                 FFTB_TUNE_MAX_CANDIDATES tilings per direction (default 16),
                                 stop after FFTB_TUNE_SECONDS (default 60) keeping the best so
                                 far, and print one progress line per trial on stderr */
-  FFTB_PLAN_GRAPH = 4,       /* replay each direction as a captured hipGraph */
+  FFTB_PLAN_GRAPH = 4,       /* replay each direction as a captured hipGraph (directions
+                                of up to 5 launches are launched: cheaper) */
   FFTB_PLAN_HOST_ONLY = 8,   /* build and validate the host tables only; no device work (testing) */
   FFTB_PLAN_MFMA = 16        /* FFTB_C64 only: radix-16 stages as FP32 MFMA dense products (the
                                 inverse fold's length-16 transforms of band-inner plans with y

@@ -1515,12 +1515,26 @@ void* plan_col(fftb_plan_s* P, bool inverse) {
   return static_cast<char*>(P->d_col) + static_cast<size_t>(P->pass_at) * es_of(P->dtype);
 }
 
+// Launches of a direction, or of the potential step (both) as axis passes.
+int launches(const fftb_plan_s& P, bool inverse, bool forward) {
+  const DirCfg& D = P.dir[inverse ? 0 : 1];
+  if (!D.pass && !(inverse && forward)) return D.fwd_cls ? 3 : 2;
+  const int ways = inverse && forward ? 2 : 1;  // (a z pass and a y pass each way, one x pass)
+  const int groups = (P.pp.nplanes + P.pp.group - 1) / P.pp.group;
+  return ways + (P.pp.plane.on ? 1 : (ways + 1) * groups);
+}
+
 // Run `enqueue(stream, profile)` on the stream, or (FFTB_PLAN_GRAPH) replay the
-// graph captured from it for these pointers.
+// graph captured from it for these pointers. Up to 5 launches go to the stream
+// themselves: a replay takes about 10 us more than they do (round trips, replayed
+// -> launched: 32^3, 4 complex128 bands, 2 launches each way, 44 -> 22 us, 256
+// complex64 bands 80 -> 70; 108x100x120, 50 bands, 5 each way, 0.510 -> 0.493 ms;
+// at 13 each way, 200x192x216, the replay is the faster by 0.01 ms of 2.29).
 template <class F>
 fftb_status run_or_replay(fftb_plan_s* P, fftb_plan_s::GraphCache& gc,
-                          const std::array<const void*, 4>& key, hipStream_t st, F&& enqueue) {
-  if (P->flags & FFTB_PLAN_GRAPH) {
+                          const std::array<const void*, 4>& key, int nlaunch, hipStream_t st, F&& enqueue) {
+  const bool graph = P->flags & FFTB_PLAN_GRAPH;
+  if (graph && nlaunch > 5) {
     if (!gc.exec || gc.key != key) {
       if (gc.exec) { (void)hipGraphExecDestroy(gc.exec); gc.exec = nullptr; }
       if (gc.graph) { (void)hipGraphDestroy(gc.graph); gc.graph = nullptr; }
@@ -1542,7 +1556,7 @@ fftb_status run_or_replay(fftb_plan_s* P, fftb_plan_s::GraphCache& gc,
     if (e != hipSuccess) return fail(FFTB_ERR_HIP, std::string("hipGraphLaunch: ") + hipGetErrorString(e));
     return FFTB_OK;
   }
-  hipError_t e = enqueue(st, P->profiling);
+  hipError_t e = enqueue(st, P->profiling && !graph);
   if (e != hipSuccess) return fail(FFTB_ERR_HIP, std::string("kernel launch: ") + hipGetErrorString(e));
   return FFTB_OK;
 }
@@ -1554,7 +1568,8 @@ fftb_status run(fftb_plan_s* P, const void* in, void* out, void* stream, bool in
   if (!in || !out) return fail(FFTB_ERR_INVALID, "null data pointer");
   if (!inverse) pot = nullptr;
   void* col = plan_col(P, inverse);
-  return run_or_replay(P, P->gc[inverse ? 0 : 1], {in, out, pot, nullptr}, static_cast<hipStream_t>(stream),
+  return run_or_replay(P, P->gc[inverse ? 0 : 1], {in, out, pot, nullptr},
+                       launches(*P, inverse, !inverse), static_cast<hipStream_t>(stream),
                        [&](hipStream_t st, bool profile) {
                          return enqueue_dir(P, in, out, inverse, pot, col, st, profile);
                        });
@@ -1566,7 +1581,7 @@ fftb_status run_potential(fftb_plan_s* P, const void* in, const void* pot, void*
   if (!P->device) return fail(FFTB_ERR_INVALID, "plan was created host-only");
   if (!in || !grid || !out) return fail(FFTB_ERR_INVALID, "null data pointer");
   void* col = plan_col(P, false);
-  return run_or_replay(P, P->gc[2], {in, grid, pot, out}, static_cast<hipStream_t>(stream),
+  return run_or_replay(P, P->gc[2], {in, grid, pot, out}, launches(*P, true, true), static_cast<hipStream_t>(stream),
                        [&](hipStream_t st, bool profile) {
                          return enqueue_pass(P, true, true, in, grid, out, pot, col, st, profile);
                        });
