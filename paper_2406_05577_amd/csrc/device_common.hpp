@@ -92,10 +92,14 @@ __device__ __forceinline__ void buf_load2(__amdgpu_buffer_rsrc_t r, unsigned vof
   b = {x.z, x.w};
 }
 
+// (No scalar offset in 16-byte stores: the compiler takes such a store to have
+// read its data a cycle earlier and may let the next instruction overwrite them,
+// which on gfx950 stored wrong words now and then. The sum stays below the span
+// of the buffer, which the host keeps below 4 GiB.)
 __device__ __forceinline__ void buf_store(__amdgpu_buffer_rsrc_t r, cpx<double> v, unsigned voff,
                                           unsigned soff) {
   typedef int v4i __attribute__((ext_vector_type(4)));
-  __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(v4i, v), r, voff, soff, 0);
+  __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(v4i, v), r, voff + soff, 0, 0);
 }
 __device__ __forceinline__ void buf_store(__amdgpu_buffer_rsrc_t r, cpx<float> v, unsigned voff,
                                           unsigned soff) {
