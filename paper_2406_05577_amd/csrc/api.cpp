@@ -176,8 +176,10 @@ struct fftb_plan_s {
   // that use them, then the passes' columns and slab planes
   int64_t class_elems(int d) const { return dir[d].pass ? 0 : dir[d].col_elems; }
   int64_t scratch_elems() const {
-    return class_elems(0) + class_elems(1) + (uses_pass() ? pp.col_elems + pp.s_elems() : 0);
+    return class_elems(0) + class_elems(1) + (uses_pass() ? pp.col_elems + slab_elems() : 0);
   }
+  // (the plane kernel holds its planes in LDS)
+  int64_t slab_elems() const { return pp.plane.on ? 0 : pp.s_elems(); }
   // per-kernel timing
   bool profiling = false;
   struct ProfRec {
@@ -840,8 +842,9 @@ void setup_passes(fftb_plan_s& P) {
   if (ok && cap) {
     // under a device memory bound: no more scratch than the class-split kernels
     const int64_t room = P.dir[0].col_elems + P.dir[1].col_elems - P.pp.col_elems;
-    ok = !P.uses_classes() && room >= P.pp.splane;
-    if (ok) P.pp.group = static_cast<int>(std::min<int64_t>(P.pp.group, room / P.pp.splane));
+    ok = !P.uses_classes() && room >= (P.pp.plane.on ? 0 : P.pp.splane);
+    if (ok && !P.pp.plane.on)
+      P.pp.group = static_cast<int>(std::min<int64_t>(P.pp.group, room / P.pp.splane));
   }
   if (!ok) P.dir[0].pass = P.dir[1].pass = false;
 }
@@ -1621,17 +1624,18 @@ void log_plan(const fftb_plan_s& P) {
                  D.fold_m);
     // the axis passes the direction takes instead
     if (D.pass) {
-      std::fprintf(stderr, "  %s: axis passes, %d groups of %d planes%s", d == 0 ? "inverse" : "forward",
-                   (P.pp.nplanes + P.pp.group - 1) / P.pp.group, P.pp.group,
-                   P.pp.two_streams() ? " halved on two streams" : "");
+      std::fprintf(stderr, "  %s: axis passes", d == 0 ? "inverse" : "forward");
+      if (P.pp.plane.on)
+        std::fprintf(stderr, ", planes in one launch, %d elements, LDS %zu B", P.pp.plane.fc, P.pp.plane.lds);
+      else
+        std::fprintf(stderr, ", %d groups of %d planes%s", (P.pp.nplanes + P.pp.group - 1) / P.pp.group,
+                     P.pp.group, P.pp.two_streams() ? " halved on two streams" : "");
       const char* name[3] = {"z", "y", "x"};
       const PassTile* tl[3] = {&P.pp.tz, &P.pp.ty, &P.pp.tx};
       const int n[3] = {P.nz, P.ny, P.nx};
-      for (int i = 0; i < 3; ++i)
+      for (int i = 0; i < (P.pp.plane.on ? 1 : 3); ++i)
         std::fprintf(stderr, ", %s %dx%d tile %d elements x %d rows, %d threads, LDS %zu B", name[i],
                      pass_r1(n[i]), n[i] / pass_r1(n[i]), tl[i]->fc, tl[i]->lines, tl[i]->threads, tl[i]->lds);
-      if (P.pp.plane.on)
-        std::fprintf(stderr, ", planes in one launch, %d elements, LDS %zu B", P.pp.plane.fc, P.pp.plane.lds);
       std::fprintf(stderr, "\n");
     }
   }

@@ -139,7 +139,7 @@ struct PassPlan {
   // bands, the potential step 5.38 -> 5.19 ms; 128^3, 256 complex64 bands, forward
   // 1.82 -> 1.74 ms). Fewer lose by the smaller launches (108x100x120, 50 complex64
   // bands, two groups: 0.497 -> 0.507 ms).
-  bool two_streams() const { return group >= 2 && nplanes > 3 * group; }
+  bool two_streams() const { return !plane.on && group >= 2 && nplanes > 3 * group; }
 };
 
 // Build the pass plan; false where a length has no split or a size does not

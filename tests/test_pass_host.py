@@ -79,3 +79,21 @@ def test_pass_scratch_under_a_bound(monkeypatch, capfd):
     scratch = float(re.search(r"scratch ([0-9.]+) GB", log).group(1))
     _, log = _log(capfd, (60, 50, 45), 16, tuning=dict(path=1))
     assert scratch <= float(re.search(r"scratch ([0-9.]+) GB", log).group(1))
+
+
+@pytest.mark.parametrize("dtype", ["c128", "c64"])
+def test_plane_kernel_plans_hold_no_slab_scratch(dtype, monkeypatch, capfd):
+    """Planes in one launch live in LDS: their plans hold the columns alone, are
+    in no plane groups and on no second stream, and a device memory bound that
+    leaves no room for a slab plane does not keep them from the passes."""
+    monkeypatch.setenv("FFTB_LOG", "1")
+    nb = 16
+    p, log = _log(capfd, (60, 54, 50), nb, "c64")
+    assert "planes in one launch" in log and "groups of" not in log and "streams" not in log
+    columns = p.info["total_columns"] * nb * 50 * 8
+    assert float(re.search(r"scratch ([0-9.]+) GB", log).group(1)) <= (columns + 50 * 128) / 1e9 + 5e-4
+    # few columns over many slabs: a slab plane is larger than the columns
+    monkeypatch.setenv("FFTB_MAX_DEVICE_BYTES", str(1 << 30))
+    lin = np.array([x + 60 * (x % 3) for x in range(0, 60, 2)], dtype=np.int32)
+    pk.Plan((60, 60, 1), [lin], 3, dtype=dtype, flags=pk.PLAN_HOST_ONLY)
+    assert capfd.readouterr().err.count("planes in one launch") == 2
