@@ -104,7 +104,9 @@ typedef struct {
 /* Tiling of one direction. A zero field means "library default". With every
  * field zero the library may run the direction as axis passes (one kernel per
  * axis, no class split) where those are faster; fftb_plan_info then reports the
- * class-split tiling that the direction would take otherwise. */
+ * class-split tiling that the direction would take otherwise. A tiling with every
+ * field as reported for a plan without a request counts as none: it gives that
+ * plan again. */
 typedef struct {
   int32_t band_chunk;   /* bands per workgroup tile, power of two, 1..64; path 3 takes one
                            128-byte piece (16 complex64 / 8 complex128 bands), and for the
@@ -151,7 +153,8 @@ typedef struct {
   int32_t max_slab;            /* max over spheres of occupied x planes */
   int64_t workspace_bytes;     /* device scratch + tables held by the plan */
   int32_t radix_x[8], radix_y[8], radix_z[8]; /* per-axis radix plan, 0-terminated */
-  fftb_tuning tuning;          /* the tiling in use */
+  fftb_tuning tuning;          /* the tiling in use, or, of a direction that runs as axis
+                                  passes, the class-split tiling it would take otherwise */
   int32_t autotuned;           /* 1 if the tiling came from timed trials, 2 if from the tuning cache */
 } fftb_plan_info;
 

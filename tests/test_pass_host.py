@@ -97,3 +97,18 @@ def test_plane_kernel_plans_hold_no_slab_scratch(dtype, monkeypatch, capfd):
     lin = np.array([x + 60 * (x % 3) for x in range(0, 60, 2)], dtype=np.int32)
     pk.Plan((60, 60, 1), [lin], 3, dtype=dtype, flags=pk.PLAN_HOST_ONLY)
     assert capfd.readouterr().err.count("planes in one launch") == 2
+
+
+@pytest.mark.parametrize("dtype", ["c128", "c64"])
+def test_reported_tiling_gives_the_plan_again(dtype, monkeypatch, capfd):
+    """A plan made with the tiling that another plan reports runs what that plan
+    runs: axis passes where it took them, or a tiling of its own that was asked for."""
+    monkeypatch.setenv("FFTB_LOG", "1")
+    for dims, nb, asked in (((108, 100, 120), 50, None), ((96, 96, 96), 63, None), ((96, 96, 96), 64, None),
+                            ((32, 32, 32), 4, None), ((6, 4, 540), 3, None), ((60, 50, 45), 7, dict(threads=128)),
+                            ((96, 96, 96), 64, dict(inv_acc=1)), ((60, 50, 45), 7, dict(fwd_threads=128))):
+        p, log = _log(capfd, dims, nb, dtype, tuning=asked)
+        again = {f"{d}_{k}": v for d in ("inv", "fwd") for k, v in p.info["tuning"][d].items()}
+        q, log2 = _log(capfd, dims, nb, dtype, tuning=again)
+        assert log2 == log, (dims, nb, asked)
+        assert q.info["tuning"] == p.info["tuning"]
