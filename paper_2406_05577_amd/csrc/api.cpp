@@ -116,7 +116,7 @@ struct DirCfg {
   int k1_tasks = 0, k2_tasks = 0, k3_tasks = 0;
   int64_t col_elems = 0;            // scratch of the class-split kernels
   bool pass = false;                // runs as axis passes instead
-  bool untuned = false;             // no tiling was asked for
+  bool untuned = false;             // the caller asked for no tiling
   SphereDesc* d_desc = nullptr;
   int32_t* d_splits = nullptr;
   void* d_twy = nullptr;
@@ -2010,6 +2010,7 @@ fftb_status fftb_plan_create(fftb_plan* out, const int32_t dims[3], const fftb_s
     }
     fftb_tuning t = {};
     if (tuning) t = *tuning;
+    const bool inv_free = same_tiling(t.inv, fftb_dir_tuning{});  // (before the tuner fills it)
     if ((flags & FFTB_PLAN_AUTOTUNE) && !(flags & FFTB_PLAN_HOST_ONLY)) {
       fftb_status st = autotune(*P, dims, spheres, nspheres, dtype, flags, t,
                                 static_cast<hipStream_t>(stream));
@@ -2019,6 +2020,7 @@ fftb_status fftb_plan_create(fftb_plan* out, const int32_t dims[3], const fftb_s
       fftb_status st = choose_dir(*P, d, d == 0 ? t.inv : t.fwd);
       if (st != FFTB_OK) return st;
     }
+    P->dir[0].untuned = P->dir[0].untuned || inv_free;
     if ((flags & FFTB_PLAN_MFMA) && !(P->dir[0].mf1 || P->dir[0].mf2 || P->dir[1].mf1 || P->dir[1].mf2))
       return fail(FFTB_ERR_UNSUPPORTED, "no DFT_16 stage for the matrix cores in this plan");
     P->pad_m = P->dir[0].fold_m;
@@ -2134,7 +2136,8 @@ fftb_status fftb_apply_potential(fftb_plan P, const void* sphere_in, const void*
     if (!P) return fail(FFTB_ERR_INVALID, "null plan");
     if (!potential) return fail(FFTB_ERR_INVALID, "null potential");
     // as passes with one x pass, which never reads the grid back, wherever the
-    // forward runs as passes and the inverse asks for no tiling (144x160x180, 128
+    // forward runs as passes and the caller asked for no tiling of the inverse (the
+    // tuner's pick for it was not timed against this step) (144x160x180, 128
     // complex128 bands, 5.42 ms against 7.26 for the two directions; 96^3, 64
     // complex64 bands, 0.36 against 0.46; 32^3, 8 complex128 bands, 24.5 against 28 us)
     if (P->dir[0].untuned && P->dir[1].pass)

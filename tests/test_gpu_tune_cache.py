@@ -38,3 +38,29 @@ def test_entries_older_than_the_passes_are_timed_again(tmp_path, monkeypatch):
     p, _ = _plan()       # and the new line is taken
     assert p.info["autotuned"] == 2
     p.close()
+
+
+def test_autotuned_plans_keep_the_fused_potential_step(tmp_path, monkeypatch):
+    """The potential step runs as passes with one x pass where the tuner, not the
+    caller, chose the inverse's tiling (no plane kernel of the forward is
+    launched), with the result of the two directions; a caller's own tiling of
+    the inverse keeps the two directions."""
+    import torch
+    cache = tmp_path / "tune.txt"
+    monkeypatch.setenv("FFTB_TUNE_CACHE", str(cache))
+    monkeypatch.setenv("FFTB_TUNE_MAX_CANDIDATES", "1")
+    _plan()
+    tag, key = cache.read_text().split()[:2]
+    cache.write_text(f"{tag} {key} 4 2 0 0 256 1 0 0 0 0 0 0 0 0 0 0 0 0\n")
+    v = torch.rand(96 * 32 * 30, dtype=torch.float64, device="cuda") - 0.5
+    out = {}
+    for name, asked, fused in (("tuned", None, True), ("asked", dict(inv_path=1), False)):
+        p, _ = _plan(asked)
+        assert p.info["autotuned"] == 2 and p.info["tuning"]["inv"]["path"] == 1
+        sph = torch.linspace(-1, 1, p.info["sphere_elems"], dtype=torch.float64, device="cuda").to(torch.complex128)
+        p.set_profiling(True)
+        out[name] = p.apply_potential(sph, v)
+        n = {k: c for k, (c, _) in p.get_profile().items()}
+        assert n["plane_inverse"] == 1 and n["plane_forward"] == (0 if fused else 1), (name, n)
+        p.close()
+    assert torch.linalg.norm(out["tuned"] - out["asked"]) <= 1e-12 * torch.linalg.norm(out["asked"])
