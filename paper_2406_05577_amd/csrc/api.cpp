@@ -804,12 +804,15 @@ bool same_tiling(const fftb_dir_tuning& a, const fftb_dir_tuning& b) {
 //     bands: 0.98 -> 0.66 ms; 56, which fill them, 0.53 -> 0.61);
 //   - complex64 with more than 8 classes re-reads the columns too often (96x192,
 //     112 bands: 0.74 -> 0.69 ms, 144x160 80: 0.64 -> 0.62; 128^2 112: 0.58 ->
-//     0.62), complex128 only on x lines of 144 points and where the columns are many
-//     (144x160x180, 4 x 32 bands 3.73 -> 3.19 ms, 16 bands 232 -> 256 us; 128x192,
-//     40 bands 0.62 -> 0.66 ms);
-//   - complex64 z lines of 144 and 160 points: the class columns' 36x4 and 40x4
-//     lines take 2.5 times the z pass (128x96x160, 4 x 64 bands, 497 against 203
-//     us; the inverse 1.83 -> 1.61 ms, 144^3 2.61 -> 2.19; 180: 247 against 221);
+//     0.62), complex128 only where the pair kernel also spills, with x lines of more
+//     than 16 values per lane, and the tasks are many (144 = 18 x 8 points, 256
+//     registers: 144x192x160, 128 bands 3.98 -> 3.36 ms, 144x256x144, 104 bands 3.74
+//     -> 3.37, 144x160x180, 4 x 32 bands 3.27 -> 3.22, but 16 bands 232 -> 256 us; 128
+//     = 16 x 8 points: 128x160x180, 4 x 32 bands 2.73 -> 2.92);
+//   - complex64 z lines without a band-inner shape, over 16 lanes in the register
+//     column kernel: it takes 2.5 times the z pass (9x16 and 10x16; 128x96x160, 4 x 64
+//     bands, 497 against 203 us; the inverse 1.83 -> 1.61 ms, 144^3 2.61 -> 2.19; the
+//     band-inner 45x4: 247 against 221 us);
 //   - too few plane tasks for the 256 CUs, one workgroup each (32^3, 4 complex128
 //     bands, 32 tasks: 23 -> 17 us), or a last round of them mostly empty: 576
 //     tasks, 96^2, 32 complex64 bands 118 -> 99 us, 16 complex128 bands 101 -> 97;
@@ -844,8 +847,10 @@ fftb_status choose_dir(fftb_plan_s& P, int d, const fftb_dir_tuning& t) {
   }
   const int64_t rounds = (tasks + 255) / 256;
   if (tasks < 256 || (5 * tasks < 4 * 256 * rounds && (!fp64 || D.n1 >= 6))) pairs = false;
-  if (fp64 ? P.nx == 144 && D.n1 > 8 && tasks >= 2048 : D.n1 > 8 || P.nz == 144 || P.nz == 160)
-    pairs = false;
+  const bool spills = fp64 && D.e2 > 16;               // the pair kernel on these x lines
+  const bool slow_columns = !fp64 && !D.bil1 && D.h1 == 16;  // register z lines
+  if (D.n1 > 8 && (!fp64 || (spills && tasks >= 2048))) pairs = false;
+  if (slow_columns) pairs = false;
   D.pass = !pairs;
   return FFTB_OK;
 }
