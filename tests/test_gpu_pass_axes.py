@@ -1,8 +1,8 @@
 """GPU parity of the axis passes as y and x passes of their own, on grids that the
 one-launch plane kernel refuses (an axis above 64 points, or more bands than its
 workgroups hold at once): every length above 64 on every axis, plane groups that
-cross spheres on one stream, buffers at any value and repeated executions. The bars
-are those of the other parity tests."""
+cross spheres on one stream, buffers at any value, repeated executions, and graph
+replays whose buffers change. The bars are those of the other parity tests."""
 import numpy as np
 import pytest
 
@@ -153,6 +153,46 @@ def test_separate_passes_repeat(dtype, capfd, monkeypatch):
     for _ in range(100):
         assert all(torch.equal(torch.view_as_real(a), torch.view_as_real(b)) for a, b in zip(results(), first))
     p.close()
+
+
+@pytest.mark.parametrize("dtype", ["c128", "c64"])
+def test_graph_replays_follow_the_buffers(dtype, capfd, monkeypatch):
+    """A graph plan with more launches than are launched directly: replayed on the
+    same buffers and captured again where any one of them changes, in both
+    directions and the potential step, beside the plain plan."""
+    import torch
+    w = synth.small_workload((80, 72, 60), (5, 5, 5), [(0.1, 0.2, -0.3)], 12, seed=92, dtype=dtype)
+    plain = make_plan(w, dtype=dtype)
+    monkeypatch.setenv("FFTB_LOG", "1")
+    monkeypatch.setenv("FFTB_MAX_DEVICE_BYTES", str(1 << 30))   # (small groups: many launches)
+    p = make_plan(w, dtype=dtype, flags=4)
+    log = capfd.readouterr().err
+    assert "axis passes" in log and int(log.split("axis passes, ")[1].split(" groups")[0]) >= 3
+    sph = to_device(np.concatenate([c.reshape(-1) for c in w.coeffs]), dtype)
+    ng, n = p.info["grid_elems"], 80 * 72 * 60
+    s = [sph, sph.flip(0).contiguous()]
+    v = [torch.rand(n, dtype=sph.real.dtype, device="cuda") - 0.5 for _ in range(2)]
+    g = [_tensor(ng, dtype) for _ in range(2)]
+    o = [_tensor(sph.numel(), dtype) for _ in range(2)]
+    want_g = [plain.sphere_to_grid(x) for x in s]
+    want_o = [plain.grid_to_sphere(x) for x in want_g]
+    for i, j in ((0, 0), (0, 0), (1, 0), (1, 1), (1, 1), (0, 1)):
+        for t in g + o:
+            t.fill_(float("nan"))
+        p.sphere_to_grid(s[i], g[j])
+        p.grid_to_sphere(want_g[i], o[j])
+        assert torch.equal(g[j], want_g[i]) and torch.equal(o[j], want_o[i]), (i, j)
+        assert torch.isnan(g[1 - j].real).all() and torch.isnan(o[1 - j].real).all()
+    vg = _tensor(ng, dtype)
+    for i, k, j, l in ((0, 0, 0, 0), (0, 0, 0, 0), (1, 0, 0, 0), (1, 1, 0, 0), (1, 1, 1, 0), (1, 1, 1, 1), (0, 1, 1, 1)):
+        for t in g + o:
+            t.fill_(float("nan"))
+        p.apply_potential(s[i], v[k], g[j], o[l])
+        want = plain.apply_potential(s[i], v[k], vg)
+        assert torch.equal(g[j], vg) and torch.equal(o[l], want), (i, k, j, l)
+        assert torch.isnan(g[1 - j].real).all() and torch.isnan(o[1 - l].real).all()
+    p.close()
+    plain.close()
 
 
 @pytest.mark.parametrize("dtype", ["c128", "c64"])
