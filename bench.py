@@ -115,7 +115,42 @@ def kernel_id(name: str):
             return fwd if n[i + len(tag):].startswith("-1") else inv
     if "k3r_kernel" in n:
         return "combine_forward"
+    # axis passes: one kernel per length (z, y and x alike), or the planes' y and x
+    # in one; `launch_ids` tells which of the direction's launches a dispatch is
+    i = n.find("pass_kernel<")
+    if i >= 0:
+        args = n[i + len("pass_kernel<"):].split(">")[0].split(",")
+        d = "potential" if args[4] == "true" else "forward" if args[0] == "-1" else "inverse"
+        return f"pass_{args[3]}_{d}"
+    i = n.find("plane_kernel<")
+    if i >= 0:
+        return "plane_" + ("inverse", "forward", "potential")[int(n[i + len("plane_kernel<")])]
     return None
+
+
+def launch_ids(names):
+    """For the kernel names of round trips in dispatch order: (library kernel id or
+    None, whether a launch of it starts there), as the library's own timing counts
+    them. Of the consecutive passes of a direction, the z pass (an inverse's first,
+    a forward's last) is its column kernel and the others together one launch of its
+    plane kernel."""
+    ids = [kernel_id(n) for n in names]
+    out = [(k, True) for k in ids]
+    lib = [i for i, k in enumerate(ids) if k is not None]
+    a = 0
+    while a < len(lib):
+        d = ids[lib[a]].rsplit("_", 1)[1]
+        b = a
+        while b < len(lib) and ids[lib[b]].startswith(("pass_", "plane_")) and ids[lib[b]].endswith("_" + d):
+            b += 1
+        run = lib[a:b]
+        if any(ids[i].startswith("pass_") for i in run):
+            z = run[0] if d == "inverse" else run[-1]
+            planes = [i for i in run if i != z]
+            for i in run:
+                out[i] = (f"column_{d}", True) if i == z else (f"plane_{d}", i == planes[0])
+        a = max(b, a + 1)
+    return out
 
 
 def _counter_rows(d: str):
@@ -130,17 +165,18 @@ def _counter_rows(d: str):
 
 
 def _per_kernel_kib(d: str, counter: str, by_id: bool):
-    """Mean counter value (KiB) per dispatch for each kernel."""
-    acc = {}
-    for r in _counter_rows(d):
-        if r["Counter_Name"] != counter:
-            continue
-        name = r["Kernel_Name"]
-        key = kernel_id(name) if by_id else name
+    """Mean counter value (KiB) per dispatch for each kernel (by_id: per launch
+    of each library kernel)."""
+    rows = sorted((r for r in _counter_rows(d) if r["Counter_Name"] == counter),
+                  key=lambda r: int(r["Dispatch_Id"]))
+    names = [r["Kernel_Name"] for r in rows]
+    total, count = {}, {}
+    for r, (key, starts) in zip(rows, launch_ids(names) if by_id else ((n, True) for n in names)):
         if key is None:
             continue
-        acc.setdefault(key, []).append(float(r["Counter_Value"]))
-    return {k: sum(v) / len(v) for k, v in acc.items()}
+        total[key] = total.get(key, 0.0) + float(r["Counter_Value"])
+        count[key] = count.get(key, 0) + starts
+    return {k: v / count[k] for k, v in total.items()}
 
 
 def summarize_counters(args):

@@ -114,3 +114,42 @@ def test_more_than_one_gpu_refused():
                        capture_output=True, text=True, timeout=120)
     assert r.returncode == 2
     assert "one GPU only" in r.stderr
+
+
+def test_counters_of_axis_passes_count_as_the_library_times_them(tmp_path, monkeypatch):
+    """z y x y x | x y x y z and the plane kernel's z yx | xy z: the z pass is the
+    column kernel, the other passes of a direction together one launch of the plane
+    kernel (on a cube the kernels of all axes have one name)."""
+    def p(sign, n=96, pot="false"):
+        return f"void fftb::pass_kernel<{sign}, double, 1, {n}, {pot}>(fftb::PassArgs)"
+
+    def plane(mode):
+        return f"void fftb::plane_kernel<{mode}, float, 2>(fftb::PlaneArgs)"
+
+    assert bench.kernel_id(p(1)) == "pass_96_inverse" and bench.kernel_id(p(-1, 144)) == "pass_144_forward"
+    assert bench.kernel_id(p(1, 60, "true")) == "pass_60_potential"
+    assert [bench.kernel_id(plane(m)) for m in range(3)] == ["plane_inverse", "plane_forward", "plane_potential"]
+    ci, pi, pf, cf = "column_inverse", "plane_inverse", "plane_forward", "column_forward"
+    trip = [p(1)] * 5 + [COPY] + [p(-1)] * 5
+    want = [(ci, True), (pi, True)] + [(pi, False)] * 3 + [(None, True), (pf, True)] + [(pf, False)] * 3 + [(cf, True)]
+    assert bench.launch_ids(trip * 2) == want * 2
+    assert bench.launch_ids([p(1), plane(0), plane(1), p(-1)]) == [(ci, True), (pi, True), (pf, True), (cf, True)]
+    assert bench.launch_ids([K1_INV, K2_INV] + [p(-1)] * 3) == [(ci, True), (pi, True), (pf, True), (pf, False), (cf, True)]
+    assert bench.launch_ids([K1_INV, K2_INV, K2_FWD, K1_FWD]) == [(ci, True), (pi, True), (pf, True), (cf, True)]
+    write_pmc(tmp_path / "c", [(1, COPY, "FETCH_SIZE", 1 << 20, 0, 1), (1, COPY, "WRITE_SIZE", 1 << 20, 0, 1)])
+    write_pmc(tmp_path / "f", [(i, n, "FETCH_SIZE", 10 + i, 0, 1) for i, n in enumerate(trip * 2)])
+    write_pmc(tmp_path / "w", [(i, n, "WRITE_SIZE", 1, 0, 1) for i, n in enumerate(trip * 2)])
+    os.makedirs(tmp_path / "profiles")
+    monkeypatch.setattr(bench, "ROOT", str(tmp_path))
+    monkeypatch.setattr(bench, "kernel_source_hash", lambda: "abc")
+
+    class A:
+        workload = "wl"
+        summarize_counters = [str(tmp_path / d) for d in ("f", "w", "c", "c")]
+
+    bench.summarize_counters(A)
+    got = json.load(open(tmp_path / "profiles" / "traffic.json"))["wl"]["bytes_per_launch"]
+    # two trips of 11 dispatches: the values of the second are 11 larger
+    mean = {ci: 10 + 5.5, pi: 4 * 5.5 + sum(range(11, 15)), pf: 4 * 5.5 + sum(range(16, 20)), cf: 20 + 5.5}
+    for k, n in ((ci, 1), (pi, 4), (pf, 4), (cf, 1)):
+        assert got[k] == pytest.approx((mean[k] + n) * 1024.0)
