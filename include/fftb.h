@@ -72,7 +72,9 @@ typedef enum {
 /* Plan flags (bitwise OR). */
 enum {
   FFTB_PLAN_PLAIN = 0,       /* one launch per kernel per call, grid sized to the work */
-  FFTB_PLAN_BATCHED = 1,     /* persistent kernels walking a device work list over all spheres */
+  FFTB_PLAN_BATCHED = 1,     /* class-split kernels as persistent kernels walking a device work
+                                list over all spheres; of no effect on directions that run as
+                                axis passes, whose launches cover all spheres either way */
   FFTB_PLAN_AUTOTUNE = 2,    /* time candidate tilings at create time and keep the fastest per
                                 direction; results are cached in the file named by the
                                 FFTB_TUNE_CACHE environment variable (default: none). The
@@ -229,7 +231,7 @@ fftb_status fftb_apply_potential(fftb_plan plan, const void* sphere_in, const vo
  * without enqueuing anything, when the plan's inverse column scratch (its
  * column slots x nz x band stride x value size) exceeds the static array.
  * Every call on one GPU shares that GPU's array: the call clears the part it
- * needs zero before its kernels run, and calls that overlap in time on one GPU
+ * needs zero (none where it runs as axis passes) before its kernels run, and calls that overlap in time on one GPU
  * (on different streams, or from different threads) race on the array. */
 fftb_status fftb_sphere_to_grid_static(fftb_plan plan, const void* sphere_in, void* grid_out,
                                        void* stream);
@@ -252,8 +254,8 @@ fftb_status fftb_plan_sphere_columns(fftb_plan plan, int32_t sphere, int32_t* co
                                      int32_t* col_y, int32_t* entry_col, int32_t* entry_z);
 
 /* Per-kernel timing of execute calls, measured with HIP events recorded on
- * the execute stream around each kernel launch (not available for graph
- * replays). Index 0: column kernel, inverse; 1: plane kernel, inverse;
+ * the execute stream around each kernel launch (not available for plans made
+ * with FFTB_PLAN_GRAPH). Index 0: column kernel, inverse; 1: plane kernel, inverse;
  * 2: plane kernel, forward; 3: column kernel, forward; 4: class combine,
  * forward (plans whose forward plane kernel writes class partials). A direction
  * that runs as axis passes counts its z pass as the column kernel and its y and

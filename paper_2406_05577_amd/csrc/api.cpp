@@ -2143,7 +2143,7 @@ fftb_status fftb_apply_potential(fftb_plan P, const void* sphere_in, const void*
     // as passes with one x pass, which never reads the grid back, wherever the
     // forward runs as passes and the caller asked for no tiling of the inverse (the
     // tuner's pick for it was not timed against this step) (144x160x180, 128
-    // complex128 bands, 5.42 ms against 7.26 for the two directions; 96^3, 64
+    // complex128 bands, 5.2 ms against 7.3 for the two directions; 96^3, 64
     // complex64 bands, 0.36 against 0.46; 32^3, 8 complex128 bands, 24.5 against 28 us)
     if (P->dir[0].untuned && P->dir[1].pass)
       return run_potential(P, sphere_in, potential, grid_work, sphere_out, stream);

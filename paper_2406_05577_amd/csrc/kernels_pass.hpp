@@ -22,26 +22,24 @@
 //
 // The potential step's x pass (POT) multiplies the inverse's rows by V on their
 // way to the grid and transforms them back in the same workgroup, into the slab
-// row that they came from: the grid is written but not read again.
-// 144x160x180, 128 complex128 bands: 2.6 ms, where the forward's x pass alone takes
-// 2.2 (the whole step 7.26 -> 5.42); its writes, grid and slab, go at 4.8 TB/s,
-// about what a pass that only writes the grid reaches. Arrays of their own after the second exchange keep it at 90
-// registers: with va and vb taken again, live wherever a lane has no item, it held
-// 132, a wave less per SIMD, and took 3.8 ms.
+// row that they came from: the grid is written but not read again. 144x160x180,
+// 128 complex128 bands: 2.6 ms, where the forward's x pass alone takes 2.2; the
+// whole step 5.2 ms, 7.3 as two directions. Arrays of their own after the second
+// exchange keep it at 90 registers: with va and vb taken again, live wherever a
+// lane has no item, it held 132, a wave less per SIMD, and took 3.8 ms.
 //
 // Bound by memory: a pass reads and writes each value once (2.4 flop per byte
 // moved at 200 points), with enough workgroups in flight: the exchange sends the
 // real and the imaginary parts one after the other, half the LDS for two more
-// barriers (144x160x180, 128 complex128 bands, a round trip: 8.80 -> 7.80 ms).
-// The y and x passes run over groups of planes whose slab scratch stays in the
+// barriers (a round trip 11 % faster at 144x160x180, 128 complex128 bands). The y
+// and x passes run over groups of planes whose slab scratch stays in the
 // last-level cache between the two, with the grid streamed past it
 // (non-temporal): a copy of that shape moved 6.7 TB/s, against 4.5 TB/s over the
 // whole scratch at once. At 144^3, 96 complex64 bands, the inverse x, y and z
-// passes move 6.1, 5.6 and 5.3 TB/s. One complex64 band per lane, no staged
-// tables -> two and staged: 128^3, 256 complex64 bands, forward 1.95 -> 1.79 ms;
-// 108x100x120, 50 bands, a round trip 0.58 -> 0.50 ms; complex128 (staged tables
-// only) 144x160x180, 128 bands, 7.08 -> 6.85 ms. At 200x192x216, 20 complex128
-// bands, a round trip takes 2.32 ms (87 ms on the LDS-stage kernels).
+// passes move 6.1, 5.6 and 5.3 TB/s. Two complex64 bands per lane and staged
+// tables are worth 8-14 % (128^3, 108x100x120), staged tables alone 3 % (complex128,
+// 144x160x180). At 200x192x216, 20 complex128 bands, a round trip takes 2.26 ms (87
+// ms on the LDS-stage kernels).
 #pragma once
 
 #include "bline.hpp"
@@ -112,10 +110,10 @@ __device__ __forceinline__ Elem<T, V> buf_ld_el(__amdgpu_buffer_rsrc_t r, unsign
   else
     return unpack<V, T>(__builtin_bit_cast(E, __builtin_amdgcn_raw_buffer_load_b64(r, off, soff, NT ? 2 : 0)));
 }
-// (No scalar offset here: the compiler takes a 16-byte store with one to have read
-// its data a cycle earlier and lets the next instruction overwrite them, which on
-// gfx950 changed the first word of a few lanes in one of 15 inverse transforms of
-// 60x54x50, 16 complex64 bands. Without one it waits.)
+// (No scalar offset here, nor in buf_store: the compiler takes a 16-byte store with
+// one to have read its data a cycle earlier and lets the next instruction overwrite
+// them, which on gfx950 changed the first word of a few lanes in one of 15 inverse
+// transforms of 60x54x50, 16 complex64 bands. Without one it waits.)
 template <bool NT, int V, typename T>
 __device__ __forceinline__ void buf_st_el(__amdgpu_buffer_rsrc_t r, T ar, T ai, T br, T bi, unsigned off) {
   const typename ElemVec<T, V>::words x = pack<V>(ar, ai, br, bi);

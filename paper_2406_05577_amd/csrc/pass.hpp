@@ -35,10 +35,10 @@ constexpr int pass_r1(int n) {
 constexpr int pass_max_threads(int n, bool small) {
   return small || pass_r1(n) <= 12 ? 1024 : 512;
 }
-// Blocks of a launch whose tiles go to the XCDs in runs of `group`.
 // Longest x and y lines of the plane kernel: second factors of at most 8.
 constexpr int kPlaneMaxN = 64;
 
+// Blocks of a launch whose tiles go to the XCDs in runs of `group`.
 constexpr int pass_grid(int total, int group) {
   return (total + 8 * group - 1) / (8 * group) * (8 * group);
 }

@@ -11,13 +11,15 @@ constexpr size_t kPassLdsMax = 160 * 1024 - 1024;
 // LDS spent on staged table rows: a few lines' worth
 constexpr size_t kPassTabMax = 8 * 1024;
 
-// A tile of a pass over lines of length n: at most 256 items per stage (four
-// waves: a fifth, mostly idle one cost the 144-point inverse passes 10-35 %,
-// and 200 points over 320 threads 10-20 %) in whole 128-byte pieces of the fast
-// dimension (nf elements of `es` bytes, the sphere's bands or its flattened
-// (line, band) index), and for short fast dimensions several rows. even: the
-// fast dimension is cut into equal shares. ragged: the band vectors are no
-// whole 128-byte lines; a tile then takes them whole where it can.
+// A tile of a pass over lines of length n: whole 128-byte pieces of the fast
+// dimension (nf elements of `es` bytes, the sphere's bands or its flattened (line,
+// band) index), as many as make 256 items per stage (four waves: a fifth, mostly
+// idle one cost the 144-point inverse passes 10-35 %, and 200 points over 320
+// threads 10-20 %) or one, all of the dimension where it is at most half longer
+// than that (384 items and more: 512 points, 8 complex64 bands), and for short
+// fast dimensions several rows. even: the fast dimension is cut into equal
+// shares. ragged: the band vectors are no whole 128-byte lines; a tile then takes
+// them whole where it can.
 bool make_tile(int n, int es, int64_t nf, int nrows, bool even, bool ragged, PassTile& t) {
   const int w = 128 / es;
   const int r1 = pass_r1(n);
